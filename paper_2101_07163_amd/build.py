@@ -15,9 +15,11 @@ ARCH = os.environ.get("SNOWLB_ARCH", "gfx950")
 
 # -packed-fp32-ops: keep the compiler from emitting packed FP32 VALU instructions (the scalar and
 # float2 code paths are used instead).
+# -amdgpu-kernarg-preload-count: the first 14 argument words arrive in scalar registers, so a workgroup of the
+# step starts with the load of its descriptor instead of with that of its arguments (128^2 step 3.8 -> 3.7 us).
 HIPCC_FLAGS = [
     "--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall",
-    "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-mllvm", "-amdgpu-kernarg-preload-count=14",
     "-I" + os.path.join(ROOT, "include"),
 ]
 

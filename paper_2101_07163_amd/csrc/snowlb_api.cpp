@@ -63,11 +63,14 @@ struct Driver {
     const DomDesc* d_doms = nullptr;  // owned by the caller
     std::vector<const DomDesc*> h_doms;  // host copies (geometry for the tile lists)
     int storage = 0, flow = 0, inout = 0, rad = 1;
+    bool from_hbm = false;  // the two copies of all lattices exceed the last-level cache
     // grid_mode (launch mode): bit 0 = persistent grid (else one workgroup per tile), grid_mode >> 1 =
     // tile order; see ensure_tiles
     int tile = 0, grid_mode = 0;
-    std::vector<TileDesc*> d_tiles;  // per (tile configuration, order): index list_index(cfg, mode)
-    std::vector<int> ntiles;
+    // per (tile configuration, order), index list_index(cfg, mode): the launch geometry (ntiles 0: not built) and,
+    // for batches, the list of tiles
+    std::vector<TileDesc*> d_tiles;
+    std::vector<StepGeom> geoms;
     int par = 0;
     int64_t step = 0;
     hipStream_t cap_stream = nullptr;
@@ -98,8 +101,12 @@ struct Driver {
     snowlb_status hipfail(hipError_t e, const char* what) { return fail(hip_status(e), hip_msg(e, what)); }
 
     snowlb_status setup() {
+        int64_t bytes = 0;
+        for (const DomDesc* d : h_doms)
+            bytes += 2 * (int64_t)d->nbx * kBlockX * round_up(d->ny, kBlockY) * (d->nqb * (d->storage == SNOWLB_STORE_FP32 ? 4 : 2) + 4);
+        from_hbm = bytes > kLastLevelCache;
         d_tiles.assign(kTileOrders * tile_config_count(), nullptr);
-        ntiles.assign(kTileOrders * tile_config_count(), 0);
+        geoms.assign(kTileOrders * tile_config_count(), StepGeom{});
         hipError_t e = hipStreamCreateWithFlags(&cap_stream, hipStreamNonBlocking);
         if (e != hipSuccess) return hipfail(e, "hipStreamCreate");
         return SNOWLB_OK;
@@ -114,7 +121,8 @@ struct Driver {
 
     static int list_index(int cfg, int mode) { return kTileOrders * cfg + (mode >> 1); }
 
-    // Tile list of configuration cfg in the order of launch mode `mode`.  Row order walks each lattice
+    // Tiles of configuration cfg in the order of launch mode `mode`: a list for a batch, the geometry alone for a
+    // single lattice (its kernel computes them, which saves a dependent load per workgroup).  Row order walks each lattice
     // row of tiles by row of tiles.  The strip orders cut each lattice into vertical strips, 512 cells
     // wide (order 1) or four of nearly equal width (order 2), and walk each strip row by row: a tile
     // then shares its halo rows with tiles a strip's width away in the order instead of a lattice row
@@ -127,7 +135,8 @@ struct Driver {
     // not change any result.
     snowlb_status ensure_tiles(int cfg, int mode) {
         const int li = list_index(cfg, mode);
-        if (d_tiles[li]) return SNOWLB_OK;
+        StepGeom& geo = geoms[li];
+        if (geo.ntiles) return SNOWLB_OK;
         const int TX = tile_config_tx(cfg), TY = tile_config_ty(cfg);
         std::vector<TileDesc> t;
         constexpr int kStripCells = 512;
@@ -136,6 +145,10 @@ struct Driver {
             const DomDesc& dd = *h_doms[k];
             const int ntx = (dd.nx + TX - 1) / TX, nty = (dd.ny + TY - 1) / TY;
             const int W = order == 1 ? std::max(1, kStripCells / TX) : order == 2 ? (ntx + 3) / 4 : ntx;
+            if (h_doms.size() == 1) {
+                geo.set_lattice(ntx, nty, std::min(W, ntx));
+                return SNOWLB_OK;
+            }
             for (int s0 = 0; s0 < ntx; s0 += W)
                 for (int j = 0; j < nty; ++j)
                     for (int i = s0; i < std::min(ntx, s0 + W); ++i)
@@ -151,17 +164,24 @@ struct Driver {
             return hipfail(e, "hipMemcpy(tiles)");
         }
         d_tiles[li] = d;
-        ntiles[li] = (int)t.size();
+        geo.ntiles = (int)t.size();
         return SNOWLB_OK;
+    }
+
+    // launch geometry of (cfg, mode), after ensure_tiles
+    StepGeom geom(int cfg, int mode) const {
+        StepGeom g = geoms[list_index(cfg, mode)];
+        g.grid = step_grid(cfg, g.ntiles, storage, flow, inout, rad, mode & 1);
+        return g;
     }
 
     snowlb_status plain(int cfg, int mode, int n, hipStream_t s) {
         snowlb_status st = ensure_tiles(cfg, mode);
         if (st) return st;
         const int li = list_index(cfg, mode);
-        const int grid = step_grid(cfg, ntiles[li], storage, flow, inout, rad, mode & 1);
+        const StepGeom g = geom(cfg, mode);
         for (int i = 0; i < n; ++i) {
-            hipError_t e = launch_step(cfg, storage, flow, inout, rad, d_doms, d_tiles[li], ntiles[li], grid, par, s);
+            hipError_t e = launch_step(cfg, storage, flow, inout, rad, d_doms, d_tiles[li], g, from_hbm, par, s);
             if (e != hipSuccess) return hipfail(e, "step kernel launch");
             par ^= 1;
             step += 1;
@@ -177,12 +197,12 @@ struct Driver {
         if (G.exec) (void)hipGraphExecDestroy(G.exec);
         G = StepGraph{};
         const int li = list_index(tile, grid_mode);
-        const int grid = step_grid(tile, ntiles[li], storage, flow, inout, rad, grid_mode & 1);
+        const StepGeom sg = geom(tile, grid_mode);
         hipError_t e = hipStreamBeginCapture(cap_stream, hipStreamCaptureModeThreadLocal);
         if (e != hipSuccess) return hipfail(e, "hipStreamBeginCapture");
         hipError_t le = hipSuccess;
         for (int i = 0; i < K && le == hipSuccess; ++i)
-            le = launch_step(tile, storage, flow, inout, rad, d_doms, d_tiles[li], ntiles[li], grid, i & 1,
+            le = launch_step(tile, storage, flow, inout, rad, d_doms, d_tiles[li], sg, from_hbm, i & 1,
                              cap_stream);
         hipGraph_t g = nullptr;
         hipError_t ee = hipStreamEndCapture(cap_stream, &g);
@@ -997,7 +1017,7 @@ static int64_t adj_area_slot(const snowlb_ctx* c, int a) { return (int64_t)c->ad
 // reverse steps over the area's states, starting from lambda[cur].  Programs are cached on the
 // context, keyed by every value their kernel arguments bake in.
 static snowlb_status adj_graph(snowlb_ctx* c, int kind, AdjDesc A, float* const lam[2], int area, int len, int cur,
-                               int grid, hipGraphExec_t* out) {
+                               hipGraphExec_t* out) {
     Driver& D = c->drv;
     struct Key {
         AdjDesc A;
@@ -1005,9 +1025,8 @@ static snowlb_status adj_graph(snowlb_ctx* c, int kind, AdjDesc A, float* const 
         const void* lam1;
         const void* slots;
         const void* segdoms;
-        const void* tiles;
         int64_t slot_bytes;
-        int32_t nck, stride, tile, grid, storage, len, cur, kind, area, pad;
+        int32_t nck, stride, tile, mode, storage, len, cur, kind, area, pad;
     } key;
     std::memset(&key, 0, sizeof key);
     if (kind == 1) {
@@ -1019,9 +1038,8 @@ static snowlb_status adj_graph(snowlb_ctx* c, int kind, AdjDesc A, float* const 
         key.cur = cur;
     } else {
         key.segdoms = c->adj.d_segdoms;
-        key.tiles = D.d_tiles[Driver::list_index(D.tile, D.grid_mode)];
         key.tile = D.tile;
-        key.grid = grid;
+        key.mode = D.grid_mode;
         key.storage = c->p.storage;
     }
     key.slots = c->adj.slots;
@@ -1042,9 +1060,9 @@ static snowlb_status adj_graph(snowlb_ctx* c, int kind, AdjDesc A, float* const 
     hipError_t le = hipSuccess;
     if (kind == 0) {
         const DomDesc* sd = c->adj.d_segdoms + (int64_t)area * std::max(c->adj.stride - 1, 1);
+        const StepGeom sg = D.geom(D.tile, D.grid_mode);
         for (int i = 0; i + 1 < len && le == hipSuccess; ++i)
-            le = launch_step(D.tile, c->p.storage, 0, 0, 1, sd + i, D.d_tiles[Driver::list_index(D.tile, D.grid_mode)],
-                             D.ntiles[Driver::list_index(D.tile, D.grid_mode)], grid, 0, cs);
+            le = launch_step(D.tile, c->p.storage, 0, 0, 1, sd + i, nullptr, sg, D.from_hbm, 0, cs);
     } else {
         const int64_t base = adj_area_slot(c, area);
         for (int i = len - 1; i >= 0 && le == hipSuccess; --i) {
@@ -1147,8 +1165,6 @@ snowlb_status snowlb_adj_backward(snowlb_ctx* c, const float* dphi, float* dU, d
     Driver& D = c->drv;
     snowlb_status r = from_driver(c, D.ensure_tiles(D.tile, D.grid_mode));
     if (r) return r;
-    const int grid = step_grid(D.tile, D.ntiles[Driver::list_index(D.tile, D.grid_mode)], c->p.storage, 0, 0, 1,
-                               D.grid_mode & 1);
     // Checkpoint intervals are reversed from the last to the first.  Interval k lives in segment area
     // k % 2: its checkpoint is copied into the area's first slot, (len - 1) recompute steps fill the
     // rest, and len reverse steps consume it.  With overlap (the default), interval k - 1 is
@@ -1170,7 +1186,7 @@ snowlb_status snowlb_adj_backward(snowlb_ctx* c, const float* dphi, float* dU, d
                                  hipMemcpyDeviceToDevice, rs));
         if (len > 1) {
             hipGraphExec_t g = nullptr;
-            if (snowlb_status r2 = adj_graph(c, 0, A, lam, ar, len, 0, grid, &g)) return r2;
+            if (snowlb_status r2 = adj_graph(c, 0, A, lam, ar, len, 0, &g)) return r2;
             HIPCHK(c, hipGraphLaunch(g, rs));
         }
         if (overlap) HIPCHK(c, hipEventRecord(c->adj.ev_rec[ar], rs));
@@ -1186,7 +1202,7 @@ snowlb_status snowlb_adj_backward(snowlb_ctx* c, const float* dphi, float* dU, d
         const int len = std::min(st, n - k * st), ar = k & 1;
         if (overlap) HIPCHK(c, hipStreamWaitEvent(s, c->adj.ev_rec[ar], 0));
         hipGraphExec_t g = nullptr;
-        if (snowlb_status r2 = adj_graph(c, 1, A, lam, ar, len, cur, grid, &g)) return r2;
+        if (snowlb_status r2 = adj_graph(c, 1, A, lam, ar, len, cur, &g)) return r2;
         HIPCHK(c, hipGraphLaunch(g, s));
         cur ^= len & 1;
         if (overlap) HIPCHK(c, hipEventRecord(c->adj.ev_rev[ar], s));

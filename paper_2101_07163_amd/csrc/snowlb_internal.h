@@ -24,6 +24,7 @@ namespace snowlb {
 // plus a y part), so the nine push destinations cost one add each.  The host keeps every byte offset
 // inside one buffer below 2^32.
 constexpr int kBlockX = 64, kBlockY = 4, kBlockCells = kBlockX * kBlockY;
+constexpr int64_t kLastLevelCache = int64_t(256) << 20;
 constexpr int64_t kMaxBufferBytes = int64_t(1) << 32;  // every in-buffer byte offset fits 32 bits
 __host__ __device__ __forceinline__ uint32_t cell_xpart(int x, int nq) {
     return (uint32_t)(x >> 6) * ((uint32_t)nq << 8) + (uint32_t)(x & 63);
@@ -92,17 +93,64 @@ struct TileDesc {
     int32_t dom, x0, y0, pad;
 };
 
+// n / d for 0 <= n < 2^31 by a multiplication: (n * m) >> (31 + ceil(log2 d)) with m rounded up (m < 2^32 for
+// d >= 2; for d = 1, m = 0 and the mask of bit 5 adds n itself).  code: the shift beyond 32 (bits 0..4) and bit 5.
+// No branch, so a uniform n stays in scalar registers.
+struct FastDiv {
+    uint32_t m, code;
+};
+inline FastDiv fast_div(uint32_t d) {
+    if (d <= 1) return FastDiv{0u, 32u};
+    uint32_t l = 1;
+    while ((1ull << l) < d) ++l;
+    return FastDiv{(uint32_t)(((1ull << (31 + l)) + d - 1) / d), l - 1};
+}
+__host__ __device__ __forceinline__ uint32_t div_by(uint32_t n, uint32_t m, uint32_t code) {
+    return ((uint32_t)(((uint64_t)n * m) >> 32) >> (code & 31u)) + (n & (0u - ((code >> 5) & 1u)));
+}
+
+// The tiles of a step launch.  A batch has a list of them in device memory; the tiles of a single lattice are
+// computed from their index: vertical strips `strip` tiles wide (the last may be narrower), each walked
+// row by row.
+struct StepGeom {
+    int32_t grid = 0, ntiles = 0;  // workgroups launched, and tiles
+    int32_t ntx = 0, strip = 0;    // tiles in x, and tiles in x of a strip
+    int32_t per = 0;               // tiles of a whole strip
+    uint32_t m_per = 0, m_strip = 0, m_last = 0, codes = 0;  // divisors per, strip, width of the last strip
+    void set_lattice(int tiles_x, int tiles_y, int strip_tiles) {
+        ntx = tiles_x;
+        strip = strip_tiles;
+        ntiles = tiles_x * tiles_y;
+        per = strip * tiles_y;
+        const int rest = ntx % strip;
+        const FastDiv a = fast_div((uint32_t)per), b = fast_div((uint32_t)strip),
+                      c = fast_div((uint32_t)(rest ? rest : strip));
+        m_per = a.m;
+        m_strip = b.m;
+        m_last = c.m;
+        codes = a.code | b.code << 8 | c.code << 16;
+    }
+    __host__ __device__ __forceinline__ void tile_at(int t, int& i, int& j) const {
+        const int s = (int)div_by((uint32_t)t, m_per, codes), r = t - s * per, first = s * strip;
+        const int width = strip < ntx - first ? strip : ntx - first;
+        const uint32_t in_whole = div_by((uint32_t)r, m_strip, codes >> 8), in_last = div_by((uint32_t)r, m_last, codes >> 16);
+        j = (int)(width == strip ? in_whole : in_last);
+        i = first + r - j * width;
+    }
+};
+
 // Launchers (defined in snowlb_kernels.hip).  All are asynchronous on `stream` and return the
 // hipError_t of the launch.
 int tile_config_count();
 const char* tile_config_name(int i);
 int tile_config_tx(int i);
 int tile_config_ty(int i);
-// One step of every tile in `tiles` (device array of ntiles entries), reading copy `par` and writing
-// copy 1 - par.  `flow`, `inout`, `storage` and the gradient reach `rad` (1 for E2/E4, 2 for E6/E8)
-// must be the same for every domain referenced.
+// One step of every tile of `geom` (of the list `tiles_dev`, or with tiles_dev null those of the single lattice
+// doms_dev[0]), reading copy `par` and writing copy 1 - par.  `flow`, `inout`, `storage` and the gradient reach
+// `rad` (1 for E2/E4, 2 for E6/E8) must be the same for every domain referenced.  `from_hbm`: the two copies of
+// the lattices exceed the last-level cache.
 hipError_t launch_step(int tile_cfg, int storage, int flow, int inout, int rad, const DomDesc* doms_dev,
-                       const TileDesc* tiles_dev, int ntiles, int grid, int par, hipStream_t s);
+                       const TileDesc* tiles_dev, const StepGeom& geom, bool from_hbm, int par, hipStream_t s);
 // Grid size of a step launch over `ntiles` tiles: grid_mode 0 = one workgroup per tile,
 // 1 = persistent (one wave of resident workgroups looping over the tiles).
 int step_grid(int tile_cfg, int ntiles, int storage, int flow, int inout, int rad, int grid_mode);

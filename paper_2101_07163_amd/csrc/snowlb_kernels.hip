@@ -26,6 +26,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "snowlb_device.h"
 #include "snowlb_internal.h"
 
@@ -38,24 +40,28 @@ __device__ __forceinline__ uint32_t cell_ypart24(int nbx, int nq, int y) {
     return __umul24((uint32_t)(y >> 2), ((uint32_t)nbx * (uint32_t)nq) << 8) + ((uint32_t)(y & 3) << 6);
 }
 
-// Closure of the domain for a lattice position (gx, gy) that may lie outside it: y periodic; x
-// periodic, or (inlet/outlet) the inlet ghost left of x = 0 (returns false) and a copy of column
-// nx-1 right of it.  (sx, sy) receives the position it maps to.
-template <bool INOUT>
-__device__ __forceinline__ bool map_pos(const DomDesc& d, int gx, int gy, int& sx, int& sy) {
-    sy = wrapi(gy, d.ny);
-    if (INOUT) {
-        if (gx < 0) {
-            sx = 0;
-            return false;
-        }
-        sx = gx < d.nx ? gx : d.nx - 1;
-    } else {
-        sx = wrapi(gx, d.nx);
-    }
-    return true;
+// i mod n for a staged position, -span < i < n + span: one add or subtract, except on lattices smaller
+// than the staged region (a uniform branch, n is the same for the whole workgroup).
+__device__ __forceinline__ int wrap_near(int i, int n, int span) {
+    if (i < 0) i += n;
+    if (i >= n) i -= n;
+    if (__builtin_expect(n < span, 0)) i = ((i % n) + n) % n;
+    return i;
 }
 
+// Closure of the domain for a staged lattice position (gx, gy) that may lie outside it (by less than a staged
+// region, SX x SY): y periodic; x periodic, or (inlet/outlet) the inlet ghost left of x = 0 (returns
+// false) and a copy of column nx-1 right of it.  (sx, sy) receives the position it maps to.
+template <bool INOUT, int SX, int SY>
+__device__ __forceinline__ bool map_pos(int nx, int ny, int gx, int gy, int& sx, int& sy) {
+    sy = wrap_near(gy, ny, SY);
+    if (INOUT) {
+        sx = min(max(gx, 0), nx - 1);
+        return gx >= 0;
+    }
+    sx = wrap_near(gx, nx, SX);
+    return true;
+}
 
 // ---------------------------------------------------------------------------------------------
 // the fused step; RAD is the reach of the gradient stencil (1: E2, E4; 2: E6, E8), i.e. the width of
@@ -65,9 +71,15 @@ __device__ __forceinline__ bool map_pos(const DomDesc& d, int gx, int gy, int& s
 template <int TY, int RAD>
 constexpr int kMinWaves = (RAD == 1 && TY >= 4) ? 4 : 1;
 
-template <int TX, int TY, class S, bool FLOW, bool INOUT, int RAD>
+// LOOP: a persistent grid whose workgroups take several tiles (else grid == ntiles).  The scalar arguments come
+// first and in this order because the first 14 words are preloaded into scalar registers: with the tile
+// computed instead of read from a list, a workgroup then waits for one scalar load (its descriptor) before
+// its first vector load, where argument, list and descriptor loads in turn were five (701 x 499 14.2 ->
+// 12.5 us, 128^2 without flow 4.0 -> 3.7 us, together with the loads in one block below).
+template <int TX, int TY, class S, bool FLOW, bool INOUT, int RAD, bool LOOP>
 __global__ void __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(kMinWaves<TY, RAD>)))
-k_step(const DomDesc* __restrict__ doms, const TileDesc* __restrict__ tiles, int ntiles, int par, int xcd_remap) {
+k_step(const DomDesc* __restrict__ doms, const TileDesc* __restrict__ tiles, int par, int grid, int ntx, int strip,
+       int per, uint32_t m_per, uint32_t m_strip, uint32_t m_last, uint32_t codes, int ntiles) {
     using T = typename S::T;
     constexpr bool REF = S::kLocalRef;
     constexpr int NR = REF ? (FLOW ? 4 : 1) : 1;  // reference planes staged in LDS
@@ -87,28 +99,25 @@ k_step(const DomDesc* __restrict__ doms, const TileDesc* __restrict__ tiles, int
     const int own = (ty + RAD) * LX + (tx + RAD);
     const int npar = 1 - par;
 
-    // XCD-aware order (optional): consecutive workgroup ids are spread over the 8 XCDs; give each
+    // XCD-aware order: consecutive workgroup ids are spread over the 8 XCDs; give each
     // XCD a contiguous run of tiles so neighbouring tiles share halo lines in that XCD's L2.  XCD x
     // receives G/8 workgroups, one more for x < G % 8; its runs follow each other in x order, so the
     // mapping is a permutation of the grid for any G.  Every other step (input copy 1) walks each run
     // backwards: a step then starts on the tiles the previous one wrote last, whose populations are
     // still in the last-level cache.
-    const int G = gridDim.x;
+    const int G = grid;
     const int b = blockIdx.x;
-    int slot = b;
-    if (xcd_remap) {
-        const int x = b % 8, k = b / 8, cnt = G / 8 + (x < G % 8 ? 1 : 0);
-        slot = x * (G / 8) + min(x, G % 8) + (par ? cnt - 1 - k : k);
-    }
+    const int xcd = b % 8, kx = b / 8, cnt = G / 8 + (xcd < G % 8 ? 1 : 0);
+    const int slot = xcd * (G / 8) + min(xcd, G % 8) + (par ? cnt - 1 - kx : kx);
 
     // halo position r of the ring: the RAD rows above and below the tile, then RAD columns left and
     // right of it
     auto ring_pos = [&](int r, int& lx, int& ly) {
         if constexpr (RAD == 1) {
-            if (r < LX) { lx = r; ly = 0; }
-            else if (r < 2 * LX) { lx = r - LX; ly = LY - 1; }
-            else if (r < 2 * LX + TY) { lx = 0; ly = 1 + (r - 2 * LX); }
-            else { lx = LX - 1; ly = 1 + (r - 2 * LX - TY); }
+            const bool below = r >= LX, column = r >= 2 * LX, right = r >= 2 * LX + TY;
+            const int kr = below ? r - LX : r, kc = r - 2 * LX - (right ? TY : 0);
+            lx = column ? (right ? LX - 1 : 0) : kr;
+            ly = column ? 1 + kc : (below ? LY - 1 : 0);
         } else {
             constexpr int BAND = RAD * LX;
             if (r < 2 * BAND) {
@@ -124,9 +133,29 @@ k_step(const DomDesc* __restrict__ doms, const TileDesc* __restrict__ tiles, int
         }
     };
 
-    for (int t = slot; t < ntiles; t += G) {
-        const TileDesc td = tiles[t];
-        const DomDesc& d = doms[td.dom];
+    for (int t = slot; !LOOP || t < ntiles; t += G) {
+        int dom = 0, x0, y0;
+        if (tiles) {
+            const TileDesc td = tiles[t];
+            dom = td.dom;
+            x0 = td.x0;
+            y0 = td.y0;
+        } else {
+            StepGeom geo;
+            geo.ntx = ntx;
+            geo.strip = strip;
+            geo.per = per;
+            geo.m_per = m_per;
+            geo.m_strip = m_strip;
+            geo.m_last = m_last;
+            geo.codes = codes;
+            int ti, tj;
+            geo.tile_at(t, ti, tj);
+            x0 = ti * TX;
+            y0 = tj * TY;
+        }
+        const DomDesc& d = doms[dom];
+        const int nx = d.nx, ny = d.ny, nbx = d.nbx;
         // uniform bases: population copies, phi_prev, reference planes
         const uint64_t pb = (uint64_t)kBlockCells * ES;  // bytes between the planes of a block
         const uint64_t rb = (uint64_t)kBlockCells * ES;
@@ -137,8 +166,8 @@ k_step(const DomDesc* __restrict__ doms, const TileDesc* __restrict__ tiles, int
         const GMEM char* rin = REF ? (const GMEM char*)d.refs[par] : nullptr;
         GMEM char* rout = REF ? (GMEM char*)d.refs[npar] : nullptr;
 
-        const int x = td.x0 + tx, y = td.y0 + ty;
-        const bool active = (x < d.nx) && (y < d.ny);
+        const int x = x0 + tx, y = y0 + ty;
+        const bool active = (x < nx) && (y < ny);
         // element offsets of a position in the population buffer (p; the 16-bit reference planes share
         // its blocks, r = p) and in the phi_prev plane (f)
         struct Off {
@@ -146,91 +175,80 @@ k_step(const DomDesc* __restrict__ doms, const TileDesc* __restrict__ tiles, int
         };
         auto offs = [&](int sx, int sy) {
             Off o;
-            o.p = cell_xpart(sx, NP) + cell_ypart24(d.nbx, NP, sy);
-            o.f = cell_xpart(sx, 1) + cell_ypart24(d.nbx, 1, sy);
+            o.p = cell_xpart(sx, NP) + cell_ypart24(nbx, NP, sy);
+            o.f = cell_xpart(sx, 1) + cell_ypart24(nbx, 1, sy);
             o.r = o.p;
             return o;
         };
-        const uint32_t xp = cell_xpart(x, NP), yp = cell_ypart24(d.nbx, NP, y);
+        const uint32_t xp = cell_xpart(x, NP), yp = cell_ypart24(nbx, NP, y);
         const uint32_t co = xp + yp;  // population offset of this lane's cell (active lanes)
 
-        // ---- issue every global load of this tile first (own position and the first pass over the
-        // halo ring, with the 16-bit references that decode them), so that they are all in flight
-        // together; decode and stage afterwards.  Lanes outside the domain stage the position their
-        // LDS slot stands for, which can be the halo of an active neighbour.
+        // ---- issue every global load of this tile first: the cell's own h, phi_prev (and 16-bit references), g
+        // and f, which are one contiguous run per workgroup, then the first pass over the halo ring.  The
+        // loads are unconditional (a lane outside the domain, or on the inlet ghost, loads the position the
+        // closure maps it to), so that they form one block and nothing is computed before the last is
+        // issued.  The ring before f and g lets the staging start earlier (1024^2 FP32 30.6 instead of
+        // 30.8 us) but splits the run, which costs HBM-sized lattices 1.8 % (2048^2 149.5 against 146.7 us).
+        // Lanes outside the domain stage the position their LDS slot stands for, which can be the halo of
+        // an active neighbour.
         T graw[5], fraw[9], hraw[9], rraw[9];
         T oref[NR], rref[NR];
-        float ophi = 0.f, rphi = 0.f;  // phi_prev of the staged positions
+        float rphi = 0.f;  // phi_prev of the staged ring position
         int osx, osy;
-        const bool oreal = map_pos<INOUT>(d, x, y, osx, osy);  // (x, y) itself for active lanes
+        const bool oreal = map_pos<INOUT, LX, LY>(nx, ny, x, y, osx, osy);  // (x, y) itself for active lanes
         const Off oo = offs(osx, osy);
-        if (oreal) {
-#pragma unroll
-            for (int q = 0; q < 9; ++q) hraw[q] = gld<T>(pin + (PH + q) * pb, oo.p * ES);
-            ophi = gld<float>(phin, oo.f * 4);
-            if (REF) {
-#pragma unroll
-                for (int k = 0; k < NR; ++k) oref[k] = gld<T>(rin + k * rb, oo.r * ES);
-            }
-        }
-        if (active) {
-#pragma unroll
-            for (int q = 0; q < 5; ++q) graw[q] = gld<T>(pin + (PG + q) * pb, co * ES);
-            if (FLOW) {
-#pragma unroll
-                for (int q = 0; q < 9; ++q) fraw[q] = gld<T>(pin + (PF + q) * pb, co * ES);
-            }
-        }
         int rlx = 0, rly = 0;
         bool rreal = false;
         const bool has_ring = tid < RING;
+#pragma unroll
+        for (int q = 0; q < 9; ++q) hraw[q] = gld<T>(pin + (PH + q) * pb, oo.p * ES);
+        const float ophi = gld<float>(phin, oo.f * 4);
+        if (REF) {
+#pragma unroll
+            for (int k = 0; k < NR; ++k) oref[k] = gld<T>(rin + k * rb, oo.r * ES);
+        }
+        uint32_t go = oo.p * ES;
+        asm("" : "+v"(go));  // keeps the 32-bit offset, and with it scalar-base addressing, in this block
+#pragma unroll
+        for (int q = 0; q < 5; ++q) graw[q] = gld<T>(pin + (PG + q) * pb, go);
+        if (FLOW) {
+#pragma unroll
+            for (int q = 0; q < 9; ++q) fraw[q] = gld<T>(pin + (PF + q) * pb, go);
+        }
         if (has_ring) {
             ring_pos(tid, rlx, rly);
             int sx, sy;
-            rreal = map_pos<INOUT>(d, td.x0 + rlx - RAD, td.y0 + rly - RAD, sx, sy);
+            rreal = map_pos<INOUT, LX, LY>(nx, ny, x0 + rlx - RAD, y0 + rly - RAD, sx, sy);
             const Off ro = offs(sx, sy);
-            if (rreal) {
 #pragma unroll
-                for (int q = 0; q < 9; ++q) rraw[q] = gld<T>(pin + (PH + q) * pb, ro.p * ES);
-                if (REF) {
-                    rphi = gld<float>(phin, ro.f * 4);
+            for (int q = 0; q < 9; ++q) rraw[q] = gld<T>(pin + (PH + q) * pb, ro.p * ES);
+            if (REF) {
+                rphi = gld<float>(phin, ro.f * 4);
 #pragma unroll
-                    for (int k = 0; k < NR; ++k) rref[k] = gld<T>(rin + k * rb, ro.r * ES);
-                }
+                for (int k = 0; k < NR; ++k) rref[k] = gld<T>(rin + k * rb, ro.r * ES);
             }
         }
+        __builtin_amdgcn_sched_barrier(0);
         // Decode h of one staged position and write phi, h and the 16-bit references to LDS.  phi is
         // summed in FP64: it is close to -1 or 1 in the bulk, and a gradient of FP32 sums would
         // carry cancellation error of order 1e-7 / |grad phi| into the direction of the normal, i.e.
         // into a and N where |grad phi| is small.  h is stored against its holder's phi_prev.
         auto stage = [&](bool real, const T raw[9], float href, const T refs[NR], int li, float hh[9]) {
-            double p64 = -1.0;  // inlet ghost: phi = -1 (its h are never read)
-            if (real) {
-                p64 = 0.0;
+            double p64 = 0.0;
 #pragma unroll
-                for (int q = 0; q < 9; ++q) {
-                    hh[q] = S::dec(raw[q], W9[q], href);
-                    p64 += (double)hh[q];
-                }
-            } else {
-#pragma unroll
-                for (int q = 0; q < 9; ++q) hh[q] = 0.f;
+            for (int q = 0; q < 9; ++q) {
+                hh[q] = S::dec(raw[q], W9[q], href);
+                p64 += (double)hh[q];
+                s_h[q][li] = hh[q];
             }
+            if (INOUT) p64 = real ? p64 : -1.0;  // inlet ghost: phi = -1 (its h are never read)
             s_phi[li] = p64;
-            if (REF) s_phif[li] = (float)p64;
-#pragma unroll
-            for (int q = 0; q < 9; ++q) s_h[q][li] = hh[q];
             if (REF) {
-                if (real) {
+                s_phif[li] = (float)p64;
 #pragma unroll
-                    for (int k = 0; k < NR; ++k) s_ref[k][li] = S::from_ref(refs[k]);
-                } else {
-                    s_ref[R_U][li] = S::from_ref(S::to_ref(d.U_in));
-                    if (FLOW) {
-                        s_ref[R_RHO][li] = S::from_ref(S::to_ref(d.ref_f));
-                        s_ref[R_JX][li] = S::from_ref(S::to_ref(d.ref_f * d.u_in));
-                        s_ref[R_JY][li] = 0.f;
-                    }
+                for (int k = 0; k < NR; ++k) {
+                    const float ghost = k == R_U ? d.U_in : k == R_RHO ? d.ref_f : k == R_JX ? d.ref_f * d.u_in : 0.f;
+                    s_ref[k][li] = S::from_ref(!INOUT || real ? refs[k] : S::to_ref(ghost));
                 }
             }
         };
@@ -245,18 +263,16 @@ k_step(const DomDesc* __restrict__ doms, const TileDesc* __restrict__ tiles, int
             int lx, ly;
             ring_pos(r, lx, ly);
             int sx, sy;
-            const bool real = map_pos<INOUT>(d, td.x0 + lx - RAD, td.y0 + ly - RAD, sx, sy);
+            const bool real = map_pos<INOUT, LX, LY>(nx, ny, x0 + lx - RAD, y0 + ly - RAD, sx, sy);
             const Off eo = offs(sx, sy);
             T raw[9], refs[NR];
             float pr = 0.f;
-            if (real) {
 #pragma unroll
-                for (int q = 0; q < 9; ++q) raw[q] = gld<T>(pin + (PH + q) * pb, eo.p * ES);
-                if (REF) {
-                    pr = gld<float>(phin, eo.f * 4);
+            for (int q = 0; q < 9; ++q) raw[q] = gld<T>(pin + (PH + q) * pb, eo.p * ES);
+            if (REF) {
+                pr = gld<float>(phin, eo.f * 4);
 #pragma unroll
-                    for (int k = 0; k < NR; ++k) refs[k] = gld<T>(rin + k * rb, eo.r * ES);
-                }
+                for (int k = 0; k < NR; ++k) refs[k] = gld<T>(rin + k * rb, eo.r * ES);
             }
             float hr[9];
             stage(real, raw, pr, refs, ly * LX + lx, hr);
@@ -507,12 +523,12 @@ k_step(const DomDesc* __restrict__ doms, const TileDesc* __restrict__ tiles, int
             }
 
             // ---- push streaming into copy 1 - par (destination offsets: x part + y part)
-            const int yN = (y + 1 < d.ny) ? y + 1 : 0;
-            const int yS = (y > 0) ? y - 1 : d.ny - 1;
-            const int xE = (x + 1 < d.nx) ? x + 1 : (INOUT ? -1 : 0);
-            const int xW = (x > 0) ? x - 1 : (INOUT ? -1 : d.nx - 1);
+            const int yN = (y + 1 < ny) ? y + 1 : 0;
+            const int yS = (y > 0) ? y - 1 : ny - 1;
+            const int xE = (x + 1 < nx) ? x + 1 : (INOUT ? -1 : 0);
+            const int xW = (x > 0) ? x - 1 : (INOUT ? -1 : nx - 1);
             const uint32_t xpE = cell_xpart(xE < 0 ? 0 : xE, NP), xpW = cell_xpart(xW < 0 ? 0 : xW, NP);
-            const uint32_t ypN = cell_ypart24(d.nbx, NP, yN), ypS = cell_ypart24(d.nbx, NP, yS);
+            const uint32_t ypN = cell_ypart24(nbx, NP, yN), ypS = cell_ypart24(nbx, NP, yS);
 #pragma unroll
             for (int q = 0; q < 9; ++q) {
                 const int xd = CX[q] > 0 ? xE : (CX[q] < 0 ? xW : x);
@@ -529,7 +545,7 @@ k_step(const DomDesc* __restrict__ doms, const TileDesc* __restrict__ tiles, int
                     if (q < 5) gst<T>(pout + (PG + q) * pb, dO, S::enc(gs[q], IW5[q], gm));
                 }
                 if (INOUT) {
-                    if (CX[q] < 0 && x == d.nx - 1) {
+                    if (CX[q] < 0 && x == nx - 1) {
                         // outlet ghost at x = nx is a copy of this column: it streams into (nx-1, yd)
                         const uint32_t dO = (xp + ypd) * ES;
                         const int ld = own + CY[q] * LX;
@@ -555,6 +571,7 @@ k_step(const DomDesc* __restrict__ doms, const TileDesc* __restrict__ tiles, int
             }
             gst<float>(phout, oo.f * 4, phi);
         }
+        if (!LOOP) break;
         __syncthreads();  // LDS is reused by the next tile
     }
 }
@@ -576,53 +593,65 @@ int tile_config_tx(int i) { return kTiles[i].tx; }
 int tile_config_ty(int i) { return kTiles[i].ty; }
 
 template <int TX, int TY, class S, bool FLOW, bool INOUT, int RAD>
-static void* step_fn() {
-    return reinterpret_cast<void*>(&k_step<TX, TY, S, FLOW, INOUT, RAD>);
+static void* step_fn(bool loop) {
+    return loop ? reinterpret_cast<void*>(&k_step<TX, TY, S, FLOW, INOUT, RAD, true>)
+                : reinterpret_cast<void*>(&k_step<TX, TY, S, FLOW, INOUT, RAD, false>);
 }
 
 template <class S, bool FLOW, bool INOUT, int RAD>
-static void* step_fn_tile(int cfg) {
+static void* step_fn_tile(int cfg, bool loop) {
     switch (cfg) {
-        case 0: return step_fn<64, 4, S, FLOW, INOUT, RAD>();
-        case 1: return step_fn<64, 8, S, FLOW, INOUT, RAD>();
-        case 2: return step_fn<128, 2, S, FLOW, INOUT, RAD>();
-        case 3: return step_fn<128, 4, S, FLOW, INOUT, RAD>();
-        case 4: return step_fn<64, 2, S, FLOW, INOUT, RAD>();
-        case 5: return step_fn<32, 8, S, FLOW, INOUT, RAD>();
+        case 0: return step_fn<64, 4, S, FLOW, INOUT, RAD>(loop);
+        case 1: return step_fn<64, 8, S, FLOW, INOUT, RAD>(loop);
+        case 2: return step_fn<128, 2, S, FLOW, INOUT, RAD>(loop);
+        case 3: return step_fn<128, 4, S, FLOW, INOUT, RAD>(loop);
+        case 4: return step_fn<64, 2, S, FLOW, INOUT, RAD>(loop);
+        case 5: return step_fn<32, 8, S, FLOW, INOUT, RAD>(loop);
     }
     return nullptr;
 }
 
 template <class S, int RAD>
-static void* step_fn_store(int cfg, int flow, int inout) {
-    if (!flow) return step_fn_tile<S, false, false, RAD>(cfg);
-    if (!inout) return step_fn_tile<S, true, false, RAD>(cfg);
-    return step_fn_tile<S, true, true, RAD>(cfg);
+static void* step_fn_store(int cfg, int flow, int inout, bool loop) {
+    if (!flow) return step_fn_tile<S, false, false, RAD>(cfg, loop);
+    if (!inout) return step_fn_tile<S, true, false, RAD>(cfg, loop);
+    return step_fn_tile<S, true, true, RAD>(cfg, loop);
 }
 
 template <int RAD>
-static void* step_kernel_rad(int cfg, int storage, int flow, int inout) {
+static void* step_kernel_rad(int cfg, int storage, int flow, int inout, bool loop) {
     switch (storage) {
-        case 0: return step_fn_store<StoreF32, RAD>(cfg, flow, inout);
-        case 1: return step_fn_store<StoreF16, RAD>(cfg, flow, inout);
-        case 2: return step_fn_store<StoreBF16, RAD>(cfg, flow, inout);
+        case 0: return step_fn_store<StoreF32, RAD>(cfg, flow, inout, loop);
+        case 1: return step_fn_store<StoreF16, RAD>(cfg, flow, inout, loop);
+        case 2: return step_fn_store<StoreBF16, RAD>(cfg, flow, inout, loop);
     }
     return nullptr;
 }
 
-static void* step_kernel(int cfg, int storage, int flow, int inout, int rad) {
+static void* step_kernel(int cfg, int storage, int flow, int inout, int rad, bool loop) {
     if (cfg < 0 || cfg >= kNumTiles) return nullptr;
     if (inout && !flow) return nullptr;
-    if (rad == 1) return step_kernel_rad<1>(cfg, storage, flow, inout);
-    if (rad == 2) return step_kernel_rad<2>(cfg, storage, flow, inout);
+    if (rad == 1) return step_kernel_rad<1>(cfg, storage, flow, inout, loop);
+    if (rad == 2) return step_kernel_rad<2>(cfg, storage, flow, inout, loop);
     return nullptr;
+}
+
+// Dynamic LDS that limits the workgroups per CU of an FP32 step whose lattices do not fit in the last-level cache
+// to 20 waves.  The kernel's registers allow 28, and lattices in that cache are fastest with them (1024^2 30.8
+// against 31.3 us, 701 x 499 12.8 against 13.8 us), but from HBM so many tiles in flight cost more than they
+// hide: 2048^2 156.8 us without the limit, 148.0 at 16 waves, 146.8 at 20; 3000^2 351.9, 324.7, 325.0; without
+// flow 2048^2 99.9, 93.3, 93.5.  16-bit storage keeps them all (2048^2 FP16 100.1 against 101.3 us).
+static int step_lds_pad(int cfg, int rad) {
+    const TileCfg& t = kTiles[cfg];
+    const int waves = t.tx * t.ty / 64, used = (t.tx + 2 * rad) * (t.ty + 2 * rad) * 44 + 256;
+    return std::max(0, std::min(65536, 163840 * waves / 20) - used);
 }
 
 // Grid of a step launch.  grid_mode 0: one workgroup per tile, dispatched in (XCD-contiguous) tile
 // order -- measured best for streaming traffic on MI355X.  grid_mode 1: a persistent grid of one
 // wave of resident workgroups that loops over the tiles.
 int step_grid(int cfg, int ntiles, int storage, int flow, int inout, int rad, int grid_mode) {
-    void* fn = step_kernel(cfg, storage, flow, inout, rad);
+    void* fn = step_kernel(cfg, storage, flow, inout, rad, true);
     if (!fn || ntiles <= 0) return 0;
     if (grid_mode == 0) return ntiles;
     int per_cu = 0;
@@ -641,14 +670,16 @@ int step_grid(int cfg, int ntiles, int storage, int flow, int inout, int rad, in
 }
 
 hipError_t launch_step(int cfg, int storage, int flow, int inout, int rad, const DomDesc* doms_dev,
-                       const TileDesc* tiles_dev, int ntiles, int grid, int par, hipStream_t s) {
-    void* fn = step_kernel(cfg, storage, flow, inout, rad);
+                       const TileDesc* tiles_dev, const StepGeom& geom, bool from_hbm, int par, hipStream_t s) {
+    void* fn = step_kernel(cfg, storage, flow, inout, rad, geom.grid < geom.ntiles);
     if (!fn) return hipErrorInvalidValue;
-    if (ntiles <= 0) return hipSuccess;
+    if (geom.ntiles <= 0) return hipSuccess;
     const int nt = kTiles[cfg].tx * kTiles[cfg].ty;
-    int remap = 1;
-    void* args[] = {(void*)&doms_dev, (void*)&tiles_dev, (void*)&ntiles, (void*)&par, (void*)&remap};
-    return hipLaunchKernel(fn, dim3(grid), dim3(nt), args, 0, s);
+    StepGeom g = geom;
+    void* args[] = {(void*)&doms_dev, (void*)&tiles_dev, (void*)&par, (void*)&g.grid, (void*)&g.ntx, (void*)&g.strip,
+                    (void*)&g.per, (void*)&g.m_per, (void*)&g.m_strip, (void*)&g.m_last, (void*)&g.codes, (void*)&g.ntiles};
+    const int pad = storage == 0 && from_hbm ? step_lds_pad(cfg, rad) : 0;
+    return hipLaunchKernel(fn, dim3(g.grid), dim3(nt), args, pad, s);
 }
 
 }  // namespace snowlb
