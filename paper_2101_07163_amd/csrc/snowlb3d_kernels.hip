@@ -366,13 +366,23 @@ __device__ __forceinline__ int64_t idx(const Dom3& d, int nq, int q, int x, int 
     return (int64_t)xpart(x, nq) + ypart(y, d.nbx, nq) + zpart(z, d.nbx, d.nby, nq) + (int64_t)q * kBlockCells;
 }
 
-__global__ void k_init3(Dom3 d, int par, const float* U_init, float U0, float sx, float sy, float sz, float R,
+// Cell of a lane: a workgroup takes one block, whose planes are contiguous in memory.
+__device__ __forceinline__ void lane_cell(int& x, int& y, int& z) {
+    const int tid = threadIdx.x;
+    x = blockIdx.x * kBX + (tid & (kBX - 1));
+    y = blockIdx.y * kBY + ((tid >> kSX) & (kBY - 1));
+    z = blockIdx.z * kBZ + (tid >> (kSX + kSY));
+}
+static dim3 block_grid(const Dom3& d) { return dim3(d.nbx, d.nby, d.nbz); }
+
+__global__ void __launch_bounds__(kBlockCells) k_init3(Dom3 d, int par, const float* U_init, float U0, float sx, float sy, float sz, float R,
                         float width) {
-    const int x = blockIdx.x * blockDim.x + threadIdx.x, y = blockIdx.y, z = blockIdx.z;
-    if (x >= d.nx) return;
+    int x, y, z;
+    lane_cell(x, y, z);
+    if (x >= d.nx || y >= d.ny || z >= d.nz) return;
     const int NP = d.npop, PG = d.flow ? 19 : 0, PH = PG + 7;
     const float dx = x - sx, dy = y - sy, dz = z - sz;
-    const float r = sqrtf(dx * dx + dy * dy + dz * dz);
+    const float r = sqrtf(__builtin_fmaf(dz, dz, __builtin_fmaf(dy, dy, dx * dx)));
     const float phi0 = tanhf((R - r) / (1.41421356237309505f * width));
     const float ux = (d.flow && d.inout) ? 0.5f * (1.f - phi0) * d.u_in : 0.f;
     const int64_t c = ((int64_t)z * d.ny + y) * d.nx + x;
@@ -407,79 +417,100 @@ __global__ void k_init3(Dom3 d, int par, const float* U_init, float U0, float sx
 
 hipError_t launch_init3(const Dom3& d, int par, const float* U_init, float U0, float sx, float sy, float sz,
                         float R, float width, hipStream_t s) {
-    hipLaunchKernelGGL(k_init3, dim3((d.nx + 127) / 128, d.ny, d.nz), dim3(128), 0, s, d, par, U_init, U0, sx, sy,
+    hipLaunchKernelGGL(k_init3, block_grid(d), dim3(kBlockCells), 0, s, d, par, U_init, U0, sx, sy,
                        sz, R, width);
     return hipGetLastError();
 }
 
-// moments of one cell: phi, U, rho and the velocity the collisions use
-__device__ void cell_fields(const Dom3& d, int par, int x, int y, int z, float out[6]) {
+// Macroscopic field read-out: one instance per kind of field, which loads only the populations that field is a
+// moment of (256 x 128 x 128, all 33 planes for any field: 110 us each).
+enum { READ_PHI, READ_U, READ_RHO, READ_VELOCITY };
+template <int KIND>
+__global__ void __launch_bounds__(kBlockCells) k_read3(Dom3 d, int par, int axis, float* __restrict__ dst) {
+    int x, y, z;
+    lane_cell(x, y, z);
+    if (x >= d.nx || y >= d.ny || z >= d.nz) return;
     const int NP = d.npop, PG = d.flow ? 19 : 0, PH = PG + 7;
-    const float* pb = d.pop[par];
-    double phi = 0.0, U = 0.0;
-    for (int q = 0; q < 7; ++q) {
-        phi += pb[idx(d, NP, PH + q, x, y, z)];
-        U += pb[idx(d, NP, PG + q, x, y, z)];
+    const float* pb = d.pop[par] + idx(d, NP, 0, x, y, z);
+    float v = 0.f, phi = 0.f;
+    if (KIND == READ_PHI || KIND == READ_U || KIND == READ_VELOCITY) {
+        double m = 0.0;
+#pragma unroll
+        for (int q = 0; q < 7; ++q) m += pb[((KIND == READ_U ? PG : PH) + q) * kBlockCells];
+        v = phi = (float)m;
     }
-    double rho = 0.0, j[3] = {0.0, 0.0, 0.0};
-    if (d.flow)
+    if (KIND == READ_RHO || KIND == READ_VELOCITY) {
+        double r = 0.0, j[3] = {0.0, 0.0, 0.0};
+#pragma unroll
         for (int q = 0; q < 19; ++q) {
-            const double v = pb[idx(d, NP, q, x, y, z)];
-            rho += v;
-            j[0] += CX[q] * v;
-            j[1] += CY[q] * v;
-            j[2] += CZ[q] * v;
+            const double f = pb[q * kBlockCells];
+            r += f;
+            j[0] += CX[q] * f;
+            j[1] += CY[q] * f;
+            j[2] += CZ[q] * f;
         }
-    out[0] = (float)phi;
-    out[1] = (float)U;
-    out[2] = d.flow ? (float)(1.0 + rho) : 0.f;
-    out[3] = out[4] = out[5] = 0.f;
-    if (d.flow) {
-        const float pc = fminf(fmaxf(out[0], -1.f), 1.f);
-        const float k = d.kdrag * (1.f + pc) * (1.f + pc) * (1.f - pc);
-        const float sc = 0.5f * (1.f - pc) / (out[2] + 0.5f * k);
-        for (int c = 0; c < 3; ++c) out[3 + c] = (float)j[c] * sc;
+        const float rho = (float)(1.0 + r);
+        v = rho;
+        if (KIND == READ_VELOCITY) {
+            const float pc = fminf(fmaxf(phi, -1.f), 1.f);
+            const float k = d.kdrag * (1.f + pc) * (1.f + pc) * (1.f - pc);
+            const float sc = 0.5f * (1.f - pc) / (rho + 0.5f * k);
+            v = (float)(axis == 0 ? j[0] : axis == 1 ? j[1] : j[2]) * sc;
+        }
     }
+    dst[((int64_t)z * d.ny + y) * d.nx + x] = v;
 }
 
-__global__ void k_read3(Dom3 d, int par, int field, float* dst) {
-    const int x = blockIdx.x * blockDim.x + threadIdx.x, y = blockIdx.y, z = blockIdx.z;
-    if (x >= d.nx) return;
-    float v[6];
-    cell_fields(d, par, x, y, z, v);
-    dst[((int64_t)z * d.ny + y) * d.nx + x] = v[field];
+// the density and velocity of a lattice without flow
+__global__ void k_fill_zero3(float* __restrict__ dst, int64_t n) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) dst[i] = 0.f;
 }
 
 hipError_t launch_read3(const Dom3& d, int par, int field, float* dst, hipStream_t s) {
     if (field < 0 || field > 5) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_read3, dim3((d.nx + 127) / 128, d.ny, d.nz), dim3(128), 0, s, d, par, field, dst);
+    const dim3 grid = block_grid(d), lanes(kBlockCells);
+    if (field == 0) hipLaunchKernelGGL(k_read3<READ_PHI>, grid, lanes, 0, s, d, par, 0, dst);
+    else if (field == 1) hipLaunchKernelGGL(k_read3<READ_U>, grid, lanes, 0, s, d, par, 0, dst);
+    else if (!d.flow) {
+        const int64_t n = (int64_t)d.nx * d.ny * d.nz;
+        hipLaunchKernelGGL(k_fill_zero3, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, dst, n);
+    } else if (field == 2) hipLaunchKernelGGL(k_read3<READ_RHO>, grid, lanes, 0, s, d, par, 0, dst);
+    else hipLaunchKernelGGL(k_read3<READ_VELOCITY>, grid, lanes, 0, s, d, par, field - 3, dst);
     return hipGetLastError();
 }
 
 // canonical FP32 [q][z][y][x] <-> the blocked layout (f is stored as f - w)
-__global__ void k_pop_io3(Dom3 d, int par, int set, int to_canon, float* canon) {
-    const int x = blockIdx.x * blockDim.x + threadIdx.x, y = blockIdx.y, z = blockIdx.z;
-    if (x >= d.nx) return;
+template <int SET>
+__global__ void __launch_bounds__(kBlockCells) k_pop_io3(Dom3 d, int par, int to_canon, float* canon) {
+    int x, y, z;
+    lane_cell(x, y, z);
+    if (x >= d.nx || y >= d.ny || z >= d.nz) return;
     const int64_t n = (int64_t)d.nx * d.ny * d.nz, c = ((int64_t)z * d.ny + y) * d.nx + x;
-    if (set == 3) {
-        float* p = &d.phip[par][idx(d, 1, 0, x, y, z)];
-        if (to_canon) canon[c] = *p;
-        else *p = canon[c];
-        return;
-    }
-    const int NP = d.npop, PG = d.flow ? 19 : 0, PH = PG + 7;
-    const int nq = set == 0 ? 19 : 7, base = set == 0 ? 0 : (set == 1 ? PG : PH);
-    for (int q = 0; q < nq; ++q) {
-        float* p = &d.pop[par][idx(d, NP, base + q, x, y, z)];
-        const float w = set == 0 ? W19[q] : 0.f;
-        if (to_canon) canon[q * n + c] = *p + w;
-        else *p = canon[q * n + c] - w;
+    constexpr int NQ = SET == 3 ? 1 : SET == 0 ? 19 : 7;
+    const int NP = d.npop, PG = d.flow ? 19 : 0, base = SET == 0 ? 0 : SET == 1 ? PG : PG + 7;
+    float* p = SET == 3 ? d.phip[par] + idx(d, 1, 0, x, y, z) : d.pop[par] + idx(d, NP, base, x, y, z);
+    const float* src = to_canon ? p : canon + c;
+    const int64_t step = to_canon ? kBlockCells : n;
+    float v[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) v[q] = src[q * step];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+        const float w = SET == 0 ? W19[q] : 0.f;
+        if (to_canon) canon[q * n + c] = SET == 0 ? v[q] + w : v[q];
+        else p[q * kBlockCells] = SET == 0 ? v[q] - w : v[q];
     }
 }
 
 hipError_t launch_pop_io3(const Dom3& d, int par, int set, int to_canon, float* canon, hipStream_t s) {
-    hipLaunchKernelGGL(k_pop_io3, dim3((d.nx + 127) / 128, d.ny, d.nz), dim3(128), 0, s, d, par, set, to_canon,
-                       canon);
+    const dim3 grid = block_grid(d), lanes(kBlockCells);
+    switch (set) {
+        case 0: hipLaunchKernelGGL(k_pop_io3<0>, grid, lanes, 0, s, d, par, to_canon, canon); break;
+        case 1: hipLaunchKernelGGL(k_pop_io3<1>, grid, lanes, 0, s, d, par, to_canon, canon); break;
+        case 2: hipLaunchKernelGGL(k_pop_io3<2>, grid, lanes, 0, s, d, par, to_canon, canon); break;
+        default: hipLaunchKernelGGL(k_pop_io3<3>, grid, lanes, 0, s, d, par, to_canon, canon);
+    }
     return hipGetLastError();
 }
 

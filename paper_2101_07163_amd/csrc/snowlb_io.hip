@@ -1,7 +1,7 @@
 // snowlb_io.hip -- set-up and read-out kernels of libsnowlb (Tan et al., arXiv:2101.07163): the
 // initial state, macroscopic field read-out and overwrite, population exchange with a canonical FP32
 // layout, FP64 diagnostics and a plain copy that measures the practical HBM ceiling.  None of them is
-// on the per-step path; they favour plain per-cell code over speed.
+// on the per-step path: plain per-cell code, laid out so that each is bound by the bytes it has to move.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
@@ -60,24 +60,84 @@ __device__ __forceinline__ void ref_at(const DomDesc& d, int par, int gx, int gy
     }
 }
 
-// Decode every population of an in-domain cell (non-hot kernels).
+// Cell of a lane: a workgroup of 256 lanes takes one 64 x 4 block, whose planes are contiguous in memory, so every
+// access of a wave is a run of 64 elements and a workgroup's accesses one range of planes.  (With rows of
+// 256 x 1 cells per workgroup each plane was four runs in four blocks: the 2048^2 FP32 initial state took
+// 83 us.)
+__device__ __forceinline__ void lane_cell(int& x, int& y) {
+    x = blockIdx.x * kBlockX + threadIdx.x % kBlockX;
+    y = blockIdx.y * kBlockY + threadIdx.x / kBlockX;
+}
+static dim3 block_grid(const DomDesc& d) { return dim3(d.nbx, (d.ny + kBlockY - 1) / kBlockY); }
+
+// Decode one population set of an in-domain cell; sets that are not asked for are not loaded.
 template <class S>
-__device__ __forceinline__ void decode_cell(const DomDesc& d, int par, int x, int y, bool flow, float f[9],
-                                            float g[5], float h[9]) {
+__device__ __forceinline__ void decode_h(const DomDesc& d, int par, int x, int y, float h[9]) {
     const int64_t i = cell_index(d.nbx, d.nqb, x, y);
     const float hr = S::kLocalRef ? phip_ptr(d, par)[cell_index(d.nbx, 1, x, y)] : 0.f;
 #pragma unroll
     for (int q = 0; q < 9; ++q) h[q] = S::dec(plane_ptr<S>(d, par, d.off_h + q)[i], W9[q], hr);
+}
+// The stored values of N planes from plane `first` on, of one cell.
+template <class S, int N>
+__device__ __forceinline__ void load_planes(const DomDesc& d, int par, int first, int x, int y, typename S::T raw[N]) {
+    const int64_t i = cell_index(d.nbx, d.nqb, x, y);
+#pragma unroll
+    for (int q = 0; q < N; ++q) raw[q] = plane_ptr<S>(d, par, first + q)[i];
+}
+// g and f take the references of their source cells from ref(dx, dy, r): of the cell at (x + dx, y + dy).
+template <class S, class R>
+__device__ __forceinline__ void decode_g(const typename S::T raw[5], const R& ref, float g[5]) {
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+        float r[4];
+        ref(-CX[q], -CY[q], r);
+        g[q] = S::dec(raw[q], W5[q], g_ref(r[R_U], r[R_JX], r[R_JY], CX[q], CY[q]));
+    }
+}
+template <class S, class R>
+__device__ __forceinline__ void decode_f(const typename S::T raw[9], const R& ref, float f[9]) {
 #pragma unroll
     for (int q = 0; q < 9; ++q) {
         float r[4];
-        ref_at<S>(d, par, x - CX[q], y - CY[q], r);
-        if (q < 5) g[q] = S::dec(plane_ptr<S>(d, par, d.off_g + q)[i], W5[q], g_ref(r[R_U], r[R_JX], r[R_JY], CX[q], CY[q]));
-        f[q] = flow ? f_abs_dec<S>(plane_ptr<S>(d, par, q)[i], q, f_ref(r[R_RHO], r[R_JX], r[R_JY], CX[q], CY[q]))
-                    : 0.f;
+        ref(-CX[q], -CY[q], r);
+        f[q] = f_abs_dec<S>(raw[q], q, f_ref(r[R_RHO], r[R_JX], r[R_JY], CX[q], CY[q]));
     }
 }
 
+// The references of a block and its one-cell ring in LDS (16-bit storage): each is formed once per position
+// instead of once per population that needs it (2048^2 FP16 from the nine sources of each cell: initial
+// state 85 us, read of rho 69 us, of U 44 us).  at(gx, gy, r) gives those of a lattice position; every lane of
+// the workgroup calls the constructor.
+template <class S>
+struct BlockRefs {
+    static constexpr int LX = kBlockX + 2, LY = kBlockY + 2, N = S::kLocalRef ? LX * LY : 1;
+    const float (*s)[N];
+    int own;
+    template <class A>
+    __device__ __forceinline__ BlockRefs(float (*lds)[N], const A& at) : s(lds) {
+        const int tid = threadIdx.x;
+        own = (tid / kBlockX + 1) * LX + tid % kBlockX + 1;
+        if (!S::kLocalRef) return;
+        const int x0 = blockIdx.x * kBlockX, y0 = blockIdx.y * kBlockY;
+        for (int p = tid; p < N; p += kBlockCells) {
+            float r[4];
+            at(x0 + p % LX - 1, y0 + p / LX - 1, r);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) lds[k][p] = r[k];
+        }
+        __syncthreads();
+    }
+    __device__ __forceinline__ void operator()(int dx, int dy, float r[4]) const {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) r[k] = S::kLocalRef ? s[k][own + dy * LX + dx] : 0.f;
+    }
+};
+template <class S>
+__device__ __forceinline__ BlockRefs<S> block_refs(const DomDesc& d, int par) {
+    __shared__ float lds[4][BlockRefs<S>::N];
+    return BlockRefs<S>(lds, [&](int gx, int gy, float r[4]) { ref_at<S>(d, par, gx, gy, r); });
+}
 
 // ---------------------------------------------------------------------------------------------
 // initial state: circular tanh seed, equilibrium populations (rest population as remainder)
@@ -90,7 +150,7 @@ struct InitArgs {
 __device__ __forceinline__ void init_at(const DomDesc& d, const InitArgs& a, int x, int y, float& phi0, float& ux,
                                         float& U) {
     const float dx = (float)x - a.sx, dy = (float)y - a.sy;
-    const float r = sqrtf(dx * dx + dy * dy);
+    const float r = sqrtf(__builtin_fmaf(dy, dy, dx * dx));
     phi0 = tanhf((a.R - r) / (1.41421356237309505f * a.width));
     ux = (d.npop == 23 && d.inout) ? 0.5f * (1.f - phi0) * a.u_in : 0.f;
     U = a.U_init ? a.U_init[(int64_t)y * d.nx + x] : a.U0;
@@ -121,9 +181,11 @@ __device__ __forceinline__ void init_ref_at(const DomDesc& d, const InitArgs& a,
 }
 
 template <class S>
-__global__ void k_init(DomDesc d, int par, InitArgs a) {
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y;
+__global__ void __launch_bounds__(kBlockCells) k_init(DomDesc d, int par, InitArgs a) {
+    int x, y;
+    lane_cell(x, y);
+    __shared__ float lds[4][BlockRefs<S>::N];
+    const BlockRefs<S> refs(lds, [&](int gx, int gy, float r[4]) { init_ref_at<S>(d, a, gx, gy, r); });
     if (x >= d.nx || y >= d.ny) return;
     const bool flow = d.npop == 23;
     const float rho0 = d.ref_f;
@@ -162,7 +224,7 @@ __global__ void k_init(DomDesc d, int par, InitArgs a) {
 #pragma unroll
     for (int q = 0; q < 9; ++q) {
         float r[4] = {0.f, 0.f, 0.f, 0.f};
-        if (S::kLocalRef) init_ref_at<S>(d, a, x - CX[q], y - CY[q], r);
+        refs(-CX[q], -CY[q], r);
         if (flow) plane_ptr_w<S>(d, par, q)[i] = f_dev_enc<S>(dfq[q], q, f_ref(r[R_RHO], r[R_JX], r[R_JY], CX[q], CY[q]));
         if (q < 5) plane_ptr_w<S>(d, par, d.off_g + q)[i] = S::enc(gq[q], IW5[q], g_ref(r[R_U], r[R_JX], r[R_JY], CX[q], CY[q]));
     }
@@ -170,8 +232,7 @@ __global__ void k_init(DomDesc d, int par, InitArgs a) {
 
 template <class S>
 static hipError_t init_s(const DomDesc& d, int par, const InitArgs& a, hipStream_t s) {
-    dim3 grid((d.nx + 255) / 256, d.ny);
-    hipLaunchKernelGGL(k_init<S>, grid, dim3(256), 0, s, d, par, a);
+    hipLaunchKernelGGL(k_init<S>, block_grid(d), dim3(kBlockCells), 0, s, d, par, a);
     return hipGetLastError();
 }
 
@@ -187,44 +248,68 @@ hipError_t launch_init(const DomDesc& d, int par, const float* U_init, float U0,
 }
 
 // ---------------------------------------------------------------------------------------------
-// macroscopic field read-out
-template <class S>
-__global__ void k_read(DomDesc d, int par, int field, float* __restrict__ dst) {
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y;
-    if (x >= d.nx || y >= d.ny) return;
-    const bool flow = d.npop == 23;
-    float f[9], g[5], h[9];
-    decode_cell<S>(d, par, x, y, flow, f, g, h);
-    double p = 0.0;
+// macroscopic field read-out.  One instance per kind of field, which loads only the populations that field is
+// a moment of: a read is bound by those bytes (2048^2 FP32, loading all 23 planes for any field: 75 us each).
+enum { READ_PHI, READ_U, READ_RHO, READ_VELOCITY };
+template <class S, int KIND>
+__global__ void __launch_bounds__(kBlockCells) k_read(DomDesc d, int par, int axis, float* __restrict__ dst) {
+    int x, y;
+    lane_cell(x, y);
+    const bool active = x < d.nx && y < d.ny;
+    float phi = 0.f, v = 0.f;
+    typename S::T graw[5], fraw[9];  // loaded before the references, which wait for a barrier
+    if (KIND == READ_U && active) load_planes<S, 5>(d, par, d.off_g, x, y, graw);
+    if ((KIND == READ_RHO || KIND == READ_VELOCITY) && active) load_planes<S, 9>(d, par, 0, x, y, fraw);
+    if ((KIND == READ_PHI || KIND == READ_VELOCITY) && active) {
+        float h[9];
+        decode_h<S>(d, par, x, y, h);
+        double p = 0.0;
 #pragma unroll
-    for (int q = 0; q < 9; ++q) p += (double)h[q];
-    const float phi = (float)p;
-    float v = 0.f;
-    if (field == 0) {
-        v = phi;
-    } else if (field == 1) {
-        v = (g[0] + g[1]) + (g[2] + g[3]) + g[4];
-    } else if (flow) {
-        const float rho = ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7])) + f[8];
-        if (field == 2) {
+        for (int q = 0; q < 9; ++q) p += (double)h[q];
+        v = phi = (float)p;
+    }
+    if constexpr (KIND != READ_PHI) {
+        const BlockRefs<S> refs = block_refs<S>(d, par);
+        if (!active) return;
+        if (KIND == READ_U) {
+            float g[5];
+            decode_g<S>(graw, refs, g);
+            v = (g[0] + g[1]) + (g[2] + g[3]) + g[4];
+        }
+        if (KIND == READ_RHO || KIND == READ_VELOCITY) {
+            float f[9];
+            decode_f<S>(fraw, refs, f);
+            const float rho = ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7])) + f[8];
             v = rho;
-        } else {
-            const float jx = (f[1] - f[3]) + (f[5] - f[6]) + (f[8] - f[7]);
-            const float jy = (f[2] - f[4]) + (f[5] + f[6]) - (f[7] + f[8]);
-            const float pc = fminf(fmaxf(phi, -1.f), 1.f);
-            const float k = d.kdrag * (1.f + pc) * (1.f + pc) * (1.f - pc);
-            const float sc = 0.5f * (1.f - pc) / (rho + 0.5f * k);
-            v = (field == 3 ? jx : jy) * sc;
+            if (KIND == READ_VELOCITY) {
+                const float jx = (f[1] - f[3]) + (f[5] - f[6]) + (f[8] - f[7]);
+                const float jy = (f[2] - f[4]) + (f[5] + f[6]) - (f[7] + f[8]);
+                const float pc = fminf(fmaxf(phi, -1.f), 1.f);
+                const float k = d.kdrag * (1.f + pc) * (1.f + pc) * (1.f - pc);
+                const float sc = 0.5f * (1.f - pc) / (rho + 0.5f * k);
+                v = (axis == 0 ? jx : jy) * sc;
+            }
         }
     }
-    dst[(int64_t)y * d.nx + x] = v;
+    if (active) dst[(int64_t)y * d.nx + x] = v;
+}
+
+// the density and velocity of a lattice without flow
+__global__ void k_fill_zero(float* __restrict__ dst, int64_t n) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) dst[i] = 0.f;
 }
 
 template <class S>
 static hipError_t read_s(const DomDesc& d, int par, int field, float* dst, hipStream_t s) {
-    dim3 grid((d.nx + 255) / 256, d.ny);
-    hipLaunchKernelGGL(k_read<S>, grid, dim3(256), 0, s, d, par, field, dst);
+    const dim3 grid = block_grid(d), lanes(kBlockCells);
+    if (field == 0) hipLaunchKernelGGL((k_read<S, READ_PHI>), grid, lanes, 0, s, d, par, 0, dst);
+    else if (field == 1) hipLaunchKernelGGL((k_read<S, READ_U>), grid, lanes, 0, s, d, par, 0, dst);
+    else if (d.npop != 23) {
+        const int64_t n = (int64_t)d.nx * d.ny;
+        hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, dst, n);
+    } else if (field == 2) hipLaunchKernelGGL((k_read<S, READ_RHO>), grid, lanes, 0, s, d, par, 0, dst);
+    else hipLaunchKernelGGL((k_read<S, READ_VELOCITY>), grid, lanes, 0, s, d, par, field - 3, dst);
     return hipGetLastError();
 }
 
@@ -244,9 +329,10 @@ hipError_t launch_read(const DomDesc& d, int par, int field, float* dst, hipStre
 // against a U reference reset to 0 (inlet-ghost sources keep the ghost constant), as a population
 // write does.  The U case reads only f, h and phi_prev, none of which it writes.
 template <class S>
-__global__ void k_write_field(DomDesc d, int par, int field, const float* __restrict__ src) {
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y;
+__global__ void __launch_bounds__(kBlockCells) k_write_field(DomDesc d, int par, int field,
+                                                             const float* __restrict__ src) {
+    int x, y;
+    lane_cell(x, y);
     if (x >= d.nx || y >= d.ny) return;
     const int64_t i = cell_index(d.nbx, d.nqb, x, y), i1 = cell_index(d.nbx, 1, x, y);
     const float v = src[(int64_t)y * d.nx + x];
@@ -264,8 +350,11 @@ __global__ void k_write_field(DomDesc d, int par, int field, const float* __rest
     const bool flow = d.npop == 23;
     float ux = 0.f, uy = 0.f;
     if (flow) {
-        float f[9], g[5], h[9];
-        decode_cell<S>(d, par, x, y, true, f, g, h);
+        float f[9], h[9];
+        typename S::T raw[9];
+        load_planes<S, 9>(d, par, 0, x, y, raw);
+        decode_f<S>(raw, [&](int dx, int dy, float r[4]) { ref_at<S>(d, par, x + dx, y + dy, r); }, f);
+        decode_h<S>(d, par, x, y, h);
         double p = 0.0;
 #pragma unroll
         for (int q = 0; q < 9; ++q) p += (double)h[q];
@@ -291,8 +380,7 @@ __global__ void k_write_field(DomDesc d, int par, int field, const float* __rest
 
 template <class S>
 static hipError_t write_field_s(const DomDesc& d, int par, int field, const float* src, hipStream_t s) {
-    dim3 grid((d.nx + 255) / 256, d.ny);
-    hipLaunchKernelGGL(k_write_field<S>, grid, dim3(256), 0, s, d, par, field, src);
+    hipLaunchKernelGGL(k_write_field<S>, block_grid(d), dim3(kBlockCells), 0, s, d, par, field, src);
     return hipGetLastError();
 }
 
@@ -307,56 +395,67 @@ hipError_t launch_write_field(const DomDesc& d, int par, int field, const float*
 
 // ---------------------------------------------------------------------------------------------
 // population sets <-> canonical FP32 [q][y][x]
-template <class S>
-__global__ void k_pop_get(DomDesc d, int par, int set, float* __restrict__ canon) {
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y;
-    if (x >= d.nx || y >= d.ny) return;
+template <class S, int SET>
+__global__ void __launch_bounds__(kBlockCells) k_pop_get(DomDesc d, int par, float* __restrict__ canon) {
+    int x, y;
+    lane_cell(x, y);
+    const bool active = x < d.nx && y < d.ny;
     const int64_t n = (int64_t)d.nx * d.ny, c = (int64_t)y * d.nx + x;
-    if (set == 3) {
-        canon[c] = phip_ptr(d, par)[cell_index(d.nbx, 1, x, y)];
-        return;
+    float v[9];
+    if constexpr (SET == 0 || SET == 1) {
+        typename S::T raw[9];
+        if (active) load_planes<S, SET == 0 ? 9 : 5>(d, par, SET == 0 ? 0 : d.off_g, x, y, raw);
+        const BlockRefs<S> refs = block_refs<S>(d, par);
+        if (!active) return;
+        if (SET == 0) decode_f<S>(raw, refs, v);
+        else decode_g<S>(raw, refs, v);
     }
-    float f[9], g[5], h[9];
-    decode_cell<S>(d, par, x, y, set == 0, f, g, h);
-    const int nq = set == 1 ? 5 : 9;
-    const float* v = set == 0 ? f : (set == 1 ? g : h);
-    for (int q = 0; q < nq; ++q) canon[q * n + c] = v[q];
+    if (!active) return;
+    if (SET == 2) decode_h<S>(d, par, x, y, v);
+    if (SET == 3) v[0] = phip_ptr(d, par)[cell_index(d.nbx, 1, x, y)];
+#pragma unroll
+    for (int q = 0; q < (SET == 3 ? 1 : SET == 1 ? 5 : 9); ++q) canon[q * n + c] = v[q];
 }
 
 // Writing a set re-encodes it against the references the step will decode it with.  Writing f
 // (resp. g) resets the rho, j (resp. U) reference planes to 0 -- any consistent reference is valid;
 // populations streamed from the inlet ghost keep the ghost's references.  Writing phi_prev
 // re-encodes h.
-template <class S>
-__global__ void k_pop_set(DomDesc d, int par, int set, const float* __restrict__ canon) {
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y;
+template <class S, int SET>
+__global__ void __launch_bounds__(kBlockCells) k_pop_set(DomDesc d, int par, const float* __restrict__ canon) {
+    int x, y;
+    lane_cell(x, y);
     if (x >= d.nx || y >= d.ny) return;
     const int64_t n = (int64_t)d.nx * d.ny, c = (int64_t)y * d.nx + x, i = cell_index(d.nbx, d.nqb, x, y);
     const int64_t i1 = cell_index(d.nbx, 1, x, y), ir = i;
+    constexpr int NQ = SET == 3 ? 1 : SET == 1 ? 5 : 9;
+    float v[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) v[q] = canon[q * n + c];
     GMEM typename S::T* wb = S::kLocalRef ? (GMEM typename S::T*)(d.refs[par]) : nullptr;
-    if (set == 0 || set == 1) {
+    if constexpr (SET == 0 || SET == 1) {
         if (S::kLocalRef) {
-            if (set == 1) wb[ir] = S::to_ref(0.f);
+            if (SET == 1) wb[ir] = S::to_ref(0.f);
             else for (int k = 1; k < 4; ++k) wb[k * d.rplane + ir] = S::to_ref(0.f);
         }
-        const int nq = set == 0 ? 9 : 5;
-        for (int q = 0; q < nq; ++q) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
             float r[4] = {0.f, 0.f, 0.f, 0.f};
             if (S::kLocalRef && d.inout && x - CX[q] < 0) ref_at<S>(d, par, -1, y - CY[q], r);  // ghost constants
-            if (set == 0)
-                plane_ptr_w<S>(d, par, q)[i] = f_abs_enc<S>(canon[q * n + c], q, f_ref(r[R_RHO], r[R_JX], r[R_JY], CX[q], CY[q]));
+            if (SET == 0)
+                plane_ptr_w<S>(d, par, q)[i] = f_abs_enc<S>(v[q], q, f_ref(r[R_RHO], r[R_JX], r[R_JY], CX[q], CY[q]));
             else
-                plane_ptr_w<S>(d, par, d.off_g + q)[i] = S::enc(canon[q * n + c], IW5[q], g_ref(r[R_U], r[R_JX], r[R_JY], CX[q], CY[q]));
+                plane_ptr_w<S>(d, par, d.off_g + q)[i] = S::enc(v[q], IW5[q], g_ref(r[R_U], r[R_JX], r[R_JY], CX[q], CY[q]));
         }
-    } else if (set == 2) {
+    } else if constexpr (SET == 2) {
         const float ref = S::kLocalRef ? phip_ptr(d, par)[i1] : 0.f;
-        for (int q = 0; q < 9; ++q) plane_ptr_w<S>(d, par, d.off_h + q)[i] = S::enc(canon[q * n + c], IW9[q], ref);
+#pragma unroll
+        for (int q = 0; q < 9; ++q) plane_ptr_w<S>(d, par, d.off_h + q)[i] = S::enc(v[q], IW9[q], ref);
     } else {
-        const float pnew = canon[c];
+        const float pnew = v[0];
         if (S::kLocalRef) {
             const float pold = phip_ptr(d, par)[i1];
+#pragma unroll
             for (int q = 0; q < 9; ++q) {
                 GMEM typename S::T* p = plane_ptr_w<S>(d, par, d.off_h + q) + i;
                 *p = S::enc(S::dec(*p, W9[q], pold), IW9[q], pnew);
@@ -366,11 +465,21 @@ __global__ void k_pop_set(DomDesc d, int par, int set, const float* __restrict__
     }
 }
 
+template <class S, int SET>
+static void pop_io_set(const DomDesc& d, int par, int to_canon, float* canon, hipStream_t s) {
+    const dim3 grid = block_grid(d), lanes(kBlockCells);
+    if (to_canon) hipLaunchKernelGGL((k_pop_get<S, SET>), grid, lanes, 0, s, d, par, canon);
+    else hipLaunchKernelGGL((k_pop_set<S, SET>), grid, lanes, 0, s, d, par, (const float*)canon);
+}
+
 template <class S>
 static hipError_t pop_io_s(const DomDesc& d, int par, int set, int to_canon, float* canon, hipStream_t s) {
-    dim3 grid((d.nx + 255) / 256, d.ny);
-    if (to_canon) hipLaunchKernelGGL(k_pop_get<S>, grid, dim3(256), 0, s, d, par, set, canon);
-    else hipLaunchKernelGGL(k_pop_set<S>, grid, dim3(256), 0, s, d, par, set, (const float*)canon);
+    switch (set) {
+        case 0: pop_io_set<S, 0>(d, par, to_canon, canon, s); break;
+        case 1: pop_io_set<S, 1>(d, par, to_canon, canon, s); break;
+        case 2: pop_io_set<S, 2>(d, par, to_canon, canon, s); break;
+        default: pop_io_set<S, 3>(d, par, to_canon, canon, s);
+    }
     return hipGetLastError();
 }
 
@@ -390,7 +499,7 @@ static constexpr int kDiagThreads = 256;
 
 int diag_blocks(const DomDesc& d) {
     const long cells = (long)d.nx * d.ny;
-    long b = (cells + kDiagThreads * 4 - 1) / (kDiagThreads * 4);
+    long b = (cells + kDiagThreads - 1) / kDiagThreads;
     if (b > kDiagMaxBlocks) b = kDiagMaxBlocks;  // larger lattices loop over more cells per thread
     return (int)(b < 1 ? 1 : b);
 }
@@ -434,9 +543,17 @@ __global__ void __launch_bounds__(kDiagThreads) k_diag(DomDesc d, int par, doubl
     const int64_t cells = (int64_t)d.nx * d.ny;
     for (int64_t c = (int64_t)blockIdx.x * kDiagThreads + threadIdx.x; c < cells;
          c += (int64_t)gridDim.x * kDiagThreads) {
-        const int y = (int)(c / d.nx), x = (int)(c - (int64_t)y * d.nx);
+        const int y = (int)((uint32_t)c / (uint32_t)d.nx), x = (int)c - y * d.nx;  // cells < 2^31
         float f[9], g[5], h[9];
-        decode_cell<S>(d, par, x, y, flow, f, g, h);
+        decode_h<S>(d, par, x, y, h);
+        const auto ref = [&](int dx, int dy, float r[4]) { ref_at<S>(d, par, x + dx, y + dy, r); };
+        typename S::T graw[5], fraw[9];
+        load_planes<S, 5>(d, par, d.off_g, x, y, graw);
+        decode_g<S>(graw, ref, g);
+        if (flow) {
+            load_planes<S, 9>(d, par, 0, x, y, fraw);
+            decode_f<S>(fraw, ref, f);
+        }
         double phi = 0, U = 0, rho = 0, jx = 0, jy = 0;
         bool bad = false;
 #pragma unroll
