@@ -103,6 +103,7 @@ void fill_dom3(snowlb3d_ctx* c) {
     d.nbx = (p.nx + kBX - 1) / kBX;
     d.nby = (p.ny + kBY - 1) / kBY;
     d.nbz = (p.nz + kBZ - 1) / kBZ;
+    set_block_order(d);
     d.flow = p.flow;
     d.npop = p.flow ? 33 : 14;
     d.inout = p.bc_x == SNOWLB_BC_INOUT;

@@ -8,6 +8,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "snowlb_div.h"
+
 namespace snowlb3d {
 
 constexpr int kBX = 64, kBY = 2, kBZ = 2, kBlockCells = kBX * kBY * kBZ;
@@ -32,7 +34,10 @@ __host__ __device__ __forceinline__ uint32_t zpart(int z, int nbx, int nby, int 
 }
 
 struct Dom3 {
-    int32_t nx, ny, nz, nbx, nby, nbz, npop, flow, inout, pad0;
+    int32_t nx, ny, nz, nbx, nby, nbz, npop, flow, inout;
+    int32_t order_lg;  // log2 of the number of slabs of the block order (block_of)
+    // divisors of the block order: nbx nbz, nby, nbx, and nbx times the two slab heights in blocks
+    snowlb::FastDiv by_layer, by_nby, by_nbx, by_low, by_high;
     float* pop[2];   // the two population copies
     float* phip[2];  // phi(t-1), one plane each
     double grad_eps2;
@@ -41,6 +46,31 @@ struct Dom3 {
     float df_in[19];  // inlet ghost f_eq(rho0, (u_in, 0, 0)) - w
     float g_in[7];    // inlet ghost g_eq(U_in, (u_in, 0, 0))
 };
+
+// Order of the blocks: the lattice is cut in y into 2^order_lg slabs whose heights in blocks differ by at most one;
+// the slabs follow each other, and each is walked z layer by z layer, rows of blocks inside a layer.
+inline void set_block_order(Dom3& d) {
+    d.order_lg = d.nby >= 8 ? 3 : 0;
+    const int low = d.nby >> d.order_lg;
+    d.by_layer = snowlb::fast_div((uint32_t)(d.nbx * d.nbz));
+    d.by_nby = snowlb::fast_div((uint32_t)d.nby);
+    d.by_nbx = snowlb::fast_div((uint32_t)d.nbx);
+    d.by_low = snowlb::fast_div((uint32_t)(d.nbx * low));
+    d.by_high = snowlb::fast_div((uint32_t)(d.nbx * (low + 1)));
+}
+__host__ __device__ __forceinline__ void block_of(const Dom3& d, int t, int& bx, int& by, int& bz) {
+    const int lg = d.order_lg, layer = d.nbx * d.nbz;
+    const int row = (int)snowlb::div_by((uint32_t)t, d.by_layer.m, d.by_layer.code);
+    const int slab = (int)snowlb::div_by((uint32_t)(((row + 1) << lg) - 1), d.by_nby.m, d.by_nby.code);
+    const int first = (slab * d.nby) >> lg, height = (((slab + 1) * d.nby) >> lg) - first;
+    const uint32_t r = (uint32_t)(t - first * layer);
+    const uint32_t in_low = snowlb::div_by(r, d.by_low.m, d.by_low.code), in_high = snowlb::div_by(r, d.by_high.m, d.by_high.code);
+    bz = (int)(height == d.nby >> lg ? in_low : in_high);
+    const uint32_t rest = r - (uint32_t)(bz * d.nbx * height);
+    const uint32_t y = snowlb::div_by(rest, d.by_nbx.m, d.by_nbx.code);
+    by = first + (int)y;
+    bx = (int)(rest - y * (uint32_t)d.nbx);
+}
 
 // One step of every block of the lattice, reading copy par and writing copy 1 - par.
 hipError_t launch_step3(const Dom3& d, const Dom3* d_dev, int par, hipStream_t s);

@@ -5,8 +5,8 @@
 // z (c) axis, a = 1 + eps Re((n_x + i n_y)^6), which is the paper's 1 + eps cos 6 theta for normals in
 // the basal plane; x periodic or inlet/outlet, y and z periodic.
 //
-// k_step3 is one fused step per block of 64 x 2 x 2 cells, built like the 2D k_step: the block's h
-// and phi (FP64) are staged with a one-cell halo in LDS (the gradient and the destination term
+// k_step3 is one fused step per block of 64 x 2 x 2 cells, built like the 2D k_step: phi (FP64) is staged with
+// a one-cell halo in LDS (the gradient), h with it where another lane needs it (the destination term
 // h_q(x + c_q, t) of Eq. (d)), each cell collides all three populations and pushes them to their
 // destinations, and every (destination, q) is written by exactly one thread.  FP32 storage; the
 // collisions close their zeroth and first moments through FP64 sums, as in 2D.
@@ -34,31 +34,6 @@ __device__ __forceinline__ void acc(double& s, int c, double v) {
     else if (c < 0) s -= v;
 }
 
-__device__ __forceinline__ int wrapi(int i, int n) {
-    if (i < 0) i += n;
-    if (i >= n) i -= n;
-    if ((unsigned)i >= (unsigned)n) i = ((i % n) + n) % n;
-    return i;
-}
-
-// Closure of a lattice position: y, z periodic; x periodic or (inlet/outlet) the inlet ghost left of
-// x = 0 (returns false) and a copy of plane nx - 1 right of it.
-template <bool INOUT>
-__device__ __forceinline__ bool map3(const Dom3& d, int gx, int gy, int gz, int& sx, int& sy, int& sz) {
-    sy = wrapi(gy, d.ny);
-    sz = wrapi(gz, d.nz);
-    if (INOUT) {
-        if (gx < 0) {
-            sx = 0;
-            return false;
-        }
-        sx = gx < d.nx ? gx : d.nx - 1;
-    } else {
-        sx = wrapi(gx, d.nx);
-    }
-    return true;
-}
-
 template <class T>
 __device__ __forceinline__ T gld(const GMEM char* base, uint32_t boff) {
     asm("" : "+s"(base));
@@ -70,82 +45,128 @@ __device__ __forceinline__ void gst(GMEM char* base, uint32_t boff, T v) {
     *(GMEM T*)(base + boff) = v;
 }
 
+// One wave per row of the block.  Its y, z and every offset made of them are uniform, so addresses are a scalar base
+// and one of three lane offsets (x, x + 1, x - 1).  Besides its own row a wave loads the three rows beside
+// it that lie outside the block (the y face, the z face and the edge between them: whole aligned rows,
+// where a scan over the 66 x 4 x 4 halo box made shifted ones in five dependent rounds) and the two columns
+// left and right of the first three.  h of a face row goes to LDS only as its share of phi, since the one
+// component a destination term takes from it is the loading lane's own.
 template <bool FLOW, bool INOUT>
-__global__ void __launch_bounds__(kBlockCells) k_step3(const Dom3* __restrict__ dp, int par, int xcd_remap) {
+__global__ void __launch_bounds__(kBlockCells) k_step3(const Dom3* __restrict__ dp, int par) {
     constexpr int LX = kBX + 2, LY = kBY + 2, LZ = kBZ + 2, LN = LX * LY * LZ;
     constexpr int NP = FLOW ? 33 : 14;                       // planes per block of a copy
     constexpr int PF = 0, PG = FLOW ? 19 : 0, PH = PG + 7;  // first plane of f, g and h
     constexpr uint32_t PB = kBlockCells * 4;                 // bytes between the planes of a block
     __shared__ double s_phi[LN];
-    __shared__ float s_h[7][LN];
+    __shared__ float s_x[2][kBY * kBZ][LX];         // h_1 and h_2 of the block's rows and columns
+    __shared__ float s_yz[4][kBY * kBZ][kBX];       // h_3 .. h_6 of the block's rows
     const Dom3& d = *dp;
+    const int nx = d.nx, ny = d.ny, nz = d.nz, nbx = d.nbx, nby = d.nby;
 
-    const int tid = threadIdx.x;
-    const int tx = tid & (kBX - 1), ty = (tid >> kSX) & (kBY - 1), tz = tid >> (kSX + kSY);
-    // XCD-aware order: each of the 8 XCDs takes a contiguous run of blocks (a permutation for any grid).
-    // Odd and even XCDs walk their runs in opposite directions, so the two XCDs on either side of a
-    // shared z-slab boundary reach it at the same time and its halo lines meet in the last-level cache;
-    // every XCD turns round every other step (input copy 1), so that a step starts on the blocks the
-    // previous one wrote last, which are still in that cache (0.2418 -> 0.2386 ms on the 256 x 128 x 128
-    // step against the same direction for all XCDs)
+    const int tid = threadIdx.x, tx = tid & (kBX - 1);
+    const int row = __builtin_amdgcn_readfirstlane(tid >> kSX), ty = row & (kBY - 1), tz = row >> kSY;
+    // XCD-aware order: each of the 8 XCDs takes a contiguous run of blocks (a permutation for any grid), which is
+    // one y slab of the block order when the lattice has eight or more block rows.  Its z neighbours are
+    // then a slab's layer away in the order (32 blocks on 256 x 128 x 128) instead of a lattice layer (256,
+    // more than the L2 holds), and the XCDs on the two sides of a slab boundary walk it at the same time,
+    // so its halo lines meet in the last-level cache: 240 -> 225 us on that lattice, 3 to 9 % on odd ones,
+    // against lattice layers (there the XCDs were better walked in alternating directions).  Every
+    // other step (input copy 1) walks backwards, so that a step starts on the blocks the previous one
+    // wrote last.
     const int G = gridDim.x, b = blockIdx.x;
-    int t = b;
-    if (xcd_remap) {
-        const int x = b % 8, k = b / 8, cnt = G / 8 + (x < G % 8 ? 1 : 0);
-        t = x * (G / 8) + min(x, G % 8) + (((x & 1) ^ par) ? cnt - 1 - k : k);
-    }
-    const int bx = t % d.nbx, by = (t / d.nbx) % d.nby, bz = t / (d.nbx * d.nby);
-    const int x0 = bx * kBX, y0 = by * kBY, z0 = bz * kBZ;
-    const int x = x0 + tx, y = y0 + ty, z = z0 + tz;
-    const bool active = x < d.nx && y < d.ny && z < d.nz;
-    const int par1 = 1 - par;
+    const int xcd = b % 8, kx = b / 8, cnt = G / 8 + (xcd < G % 8 ? 1 : 0);
+    const int back = par ^ (d.order_lg ? 0 : (xcd & 1));
+    int bx, by, bz;
+    block_of(d, xcd * (G / 8) + min(xcd, G % 8) + (back ? cnt - 1 - kx : kx), bx, by, bz);
+    const int x0 = bx * kBX, x = x0 + tx, y = by * kBY + ty, z = bz * kBZ + tz;
+    const bool active = x < nx && y < ny && z < nz;
     const GMEM char* pin = (const GMEM char*)d.pop[par];
-    GMEM char* pout = (GMEM char*)d.pop[par1];
+    GMEM char* pout = (GMEM char*)d.pop[1 - par];
     const GMEM char* phin = (const GMEM char*)d.phip[par];
-    GMEM char* phout = (GMEM char*)d.phip[par1];
+    GMEM char* phout = (GMEM char*)d.phip[1 - par];
 
-    const uint32_t xp = xpart(x, NP), yp = ypart(y, d.nbx, NP), zp = zpart(z, d.nbx, d.nby, NP);
-    const uint32_t co = xp + yp + zp;
-    const uint32_t cf = xpart(x, 1) + ypart(y, d.nbx, 1) + zpart(z, d.nbx, d.nby, 1);
+    // Rows as byte offsets into the population buffer, of a y and a z one step outside the lattice at most (every
+    // side has at least two cells).
+    auto wrap = [](int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); };
+    auto yof = [&](int gy) { return ypart(wrap(gy, ny), nbx, NP) * 4u; };
+    auto zof = [&](int gz) { return zpart(wrap(gz, nz), nbx, nby, NP) * 4u; };
+    const uint32_t yo = yof(y), zo = zof(z);
+    const uint32_t yf = yof(ty ? y + 1 : y - 1), zf = zof(tz ? z + 1 : z - 1);  // the rows outside the block
+    // x of a staged position: the outlet repeats the last column, the inlet ghost is masked below, periodic wraps
+    // (more than once on a lattice narrower than the block: a uniform branch)
+    auto xof = [&](int gx) {
+        if (INOUT) return xpart(min(max(gx, 0), nx - 1), NP) * 4u;
+        int i = wrap(gx, nx);
+        if (__builtin_expect(nx < LX, 0)) i = ((i % nx) + nx) % nx;
+        return xpart(i, NP) * 4u;
+    };
+    const uint32_t xo = xof(x);
+    // columns: lanes 0..5 of a wave take the left and right column of its own, y face and z face rows
+    const int ckind = (tx >> 1) % 3, cside = tx & 1, cx = cside ? x0 + kBX : x0 - 1;
+    const uint32_t co = xof(cx) + (ckind == 1 ? yf + zo : ckind == 2 ? yo + zf : yo + zo);
 
-    // the cell's own flow, vapour and phi_prev first, then the halo box of h
-    float f[19], g[7], phip = 0.f;
-    if (active) {
+    // ---- every global load: the own row's f, g, h and phi_prev, then the halo rows of h and the columns
+    float f[19], g[7], h[7], hy[7], hz[7], he[7], hc[7];
+    const GMEM char* prow = pin + (yo + zo);
+    if (FLOW) {
 #pragma unroll
-        for (int q = 0; q < 7; ++q) g[q] = gld<float>(pin + (PG + q) * PB, co * 4);
-        if (FLOW) {
-#pragma unroll
-            for (int q = 0; q < 19; ++q) f[q] = gld<float>(pin + (PF + q) * PB, co * 4);
-        }
-        phip = gld<float>(phin, cf * 4);
+        for (int q = 0; q < 19; ++q) f[q] = gld<float>(prow + (PF + q) * PB, xo);
     }
-    for (int p = tid; p < LN; p += kBlockCells) {
-        const int lx = p % LX, ly = (p / LX) % LY, lz = p / (LX * LY);
-        int sx, sy, sz;
-        const bool real = map3<INOUT>(d, x0 + lx - 1, y0 + ly - 1, z0 + lz - 1, sx, sy, sz);
-        double p64 = -1.0;  // inlet ghost: phi = -1 (its h are never read)
-        float hh[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        if (real) {
-            const uint32_t o = xpart(sx, NP) + ypart(sy, d.nbx, NP) + zpart(sz, d.nbx, d.nby, NP);
-            p64 = 0.0;
 #pragma unroll
-            for (int q = 0; q < 7; ++q) {
-                hh[q] = gld<float>(pin + (PH + q) * PB, o * 4);
-                p64 += (double)hh[q];
-            }
-        }
-        s_phi[p] = p64;
+    for (int q = 0; q < 7; ++q) g[q] = gld<float>(prow + (PG + q) * PB, xo);
 #pragma unroll
-        for (int q = 0; q < 7; ++q) s_h[q][p] = hh[q];
+    for (int q = 0; q < 7; ++q) h[q] = gld<float>(prow + (PH + q) * PB, xo);
+    const uint32_t cf = (xpart(min(x, nx - 1), 1) + ypart(min(y, ny - 1), nbx, 1) + zpart(min(z, nz - 1), nbx, nby, 1)) * 4u;
+    const float phip = gld<float>(phin, cf);
+#pragma unroll
+    for (int q = 0; q < 7; ++q) hy[q] = gld<float>(pin + (yf + zo) + (PH + q) * PB, xo);
+#pragma unroll
+    for (int q = 0; q < 7; ++q) hz[q] = gld<float>(pin + (yo + zf) + (PH + q) * PB, xo);
+#pragma unroll
+    for (int q = 0; q < 7; ++q) he[q] = gld<float>(pin + (yf + zf) + (PH + q) * PB, xo);
+    if (tx < 6) {
+#pragma unroll
+        for (int q = 0; q < 7; ++q) hc[q] = gld<float>(pin + (PH + q) * PB, co);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- staging.  phi is summed in FP64 in the order of q.
+    auto sum7 = [](const float v[7]) {
+        double p = 0.0;
+#pragma unroll
+        for (int q = 0; q < 7; ++q) p += (double)v[q];
+        return p;
+    };
+    const int ly = ty + 1, lz = tz + 1, fy = ty ? LY - 1 : 0, fz = tz ? LZ - 1 : 0;
+    auto slot = [&](int sy, int sz) { return (sz * LY + sy) * LX; };
+    const int own = slot(ly, lz) + tx + 1;
+    const double phi64 = sum7(h);
+    s_phi[own] = phi64;
+    s_x[0][row][tx + 1] = h[1];
+    s_x[1][row][tx + 1] = h[2];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s_yz[q][row][tx] = h[3 + q];
+    s_phi[slot(fy, lz) + tx + 1] = sum7(hy);
+    s_phi[slot(ly, fz) + tx + 1] = sum7(hz);
+    s_phi[slot(fy, fz) + tx + 1] = sum7(he);
+    if (tx < 6) {
+        const int at = ckind == 1 ? slot(fy, lz) : ckind == 2 ? slot(ly, fz) : slot(ly, lz);
+        double p64 = sum7(hc);
+        if (INOUT && cx < 0) p64 = -1.0;  // inlet ghost: phi = -1 (its h are never used)
+        s_phi[at + (cside ? LX - 1 : 0)] = p64;
+        if (ckind == 0) s_x[1 - cside][row][cside ? LX - 1 : 0] = hc[2 - cside];
     }
     __syncthreads();
     if (!active) return;  // no barrier follows
 
-    const int own = ((tz + 1) * LY + (ty + 1)) * LX + (tx + 1);
-    float h[7];
-#pragma unroll
-    for (int q = 0; q < 7; ++q) h[q] = s_h[q][own];
-    const double phi64 = s_phi[own];
+    // h_q at the destination x + c_q, q = 1..6: a lane or a row of the block away, or the face row's own value
+    const float hd[7] = {h[0],
+                         s_x[0][row][tx + 2],
+                         s_x[1][row][tx],
+                         ty ? hy[3] : s_yz[0][row + 1 - ty][tx],
+                         ty ? s_yz[1][row - ty][tx] : hy[4],
+                         tz ? hz[5] : s_yz[2][row + kBY - kBY * tz][tx],
+                         tz ? s_yz[3][row - kBY * tz][tx] : hz[6]};
     const float phi = (float)phi64;
 
     // isotropic gradient over the 18 D3Q19 neighbours, FP64: differences across each pair of
@@ -298,51 +319,44 @@ __global__ void __launch_bounds__(kBlockCells) k_step3(const Dom3* __restrict__ 
     }
 
     // push streaming into copy 1 - par; destinations with the closure
-    const int yN = y + 1 < d.ny ? y + 1 : 0, yS = y > 0 ? y - 1 : d.ny - 1;
-    const int zU = z + 1 < d.nz ? z + 1 : 0, zD = z > 0 ? z - 1 : d.nz - 1;
-    const int xE = x + 1 < d.nx ? x + 1 : (INOUT ? -1 : 0);
-    const int xW = x > 0 ? x - 1 : (INOUT ? -1 : d.nx - 1);
-    const uint32_t xpE = xpart(xE < 0 ? 0 : xE, NP), xpW = xpart(xW < 0 ? 0 : xW, NP);
-    const uint32_t ypN = ypart(yN, d.nbx, NP), ypS = ypart(yS, d.nbx, NP);
-    const uint32_t zpU = zpart(zU, d.nbx, d.nby, NP), zpD = zpart(zD, d.nbx, d.nby, NP);
+    const uint32_t yN = yof(y + 1), yS = yof(y - 1), zU = zof(z + 1), zD = zof(z - 1);
+    const int xE = x + 1 < nx ? x + 1 : (INOUT ? -1 : 0);
+    const int xW = x > 0 ? x - 1 : (INOUT ? -1 : nx - 1);
+    const uint32_t xoE = xpart(xE < 0 ? 0 : xE, NP) * 4u, xoW = xpart(xW < 0 ? 0 : xW, NP) * 4u;
 #pragma unroll
     for (int q = 0; q < 19; ++q) {
         if (!FLOW && q >= 7) break;
         const int xd = CX[q] > 0 ? xE : (CX[q] < 0 ? xW : x);
-        const uint32_t xo = CX[q] > 0 ? xpE : (CX[q] < 0 ? xpW : xp);
-        const uint32_t yo = CY[q] > 0 ? ypN : (CY[q] < 0 ? ypS : yp);
-        const uint32_t zo = CZ[q] > 0 ? zpU : (CZ[q] < 0 ? zpD : zp);
-        const int lq = own + (CZ[q] * LY + CY[q]) * LX + CX[q];  // destination in the halo box
+        const uint32_t xq = CX[q] > 0 ? xoE : (CX[q] < 0 ? xoW : xo);
+        GMEM char* pq = pout + ((CY[q] > 0 ? yN : (CY[q] < 0 ? yS : yo)) + (CZ[q] > 0 ? zU : (CZ[q] < 0 ? zD : zo)));
         if (xd >= 0) {
-            const uint32_t dO = (xo + yo + zo) * 4;
             if (q < 7) {
-                gst<float>(pout + (PH + q) * PB, dO, P7[q] - B * s_h[q][lq]);
-                gst<float>(pout + (PG + q) * PB, dO, gs[q]);
+                gst<float>(pq + (PH + q) * PB, xq, P7[q] - B * hd[q]);
+                gst<float>(pq + (PG + q) * PB, xq, gs[q]);
             }
-            if (FLOW) gst<float>(pout + (PF + q) * PB, dO, fs[q]);
+            if (FLOW) gst<float>(pq + (PF + q) * PB, xq, fs[q]);
         }
         if (INOUT) {
-            if (CX[q] < 0 && x == d.nx - 1) {
+            if (CX[q] < 0 && x == nx - 1) {
                 // the outlet ghost at x = nx copies this plane: it streams into (nx-1, y + cy, z + cz)
-                const uint32_t dO = (xp + yo + zo) * 4;
-                const int ld = own + (CZ[q] * LY + CY[q]) * LX;
                 if (q < 7) {
-                    gst<float>(pout + (PH + q) * PB, dO, P7[q] - B * s_h[q][ld]);
-                    gst<float>(pout + (PG + q) * PB, dO, gs[q]);
+                    gst<float>(pq + (PH + q) * PB, xo, P7[q] - B * h[q]);
+                    gst<float>(pq + (PG + q) * PB, xo, gs[q]);
                 }
-                gst<float>(pout + (PF + q) * PB, dO, fs[q]);
+                gst<float>(pq + (PF + q) * PB, xo, fs[q]);
             }
             if (CX[q] > 0 && x == 0) {
                 // the inlet ghost at x = -1: equilibrium (rho0, (u_in, 0, 0); U_in; phi = -1)
+                GMEM char* po = pout + (yo + zo);
                 if (q < 7) {
-                    gst<float>(pout + (PH + q) * PB, co * 4, -W7[q]);
-                    gst<float>(pout + (PG + q) * PB, co * 4, d.g_in[q]);
+                    gst<float>(po + (PH + q) * PB, xo, -W7[q]);
+                    gst<float>(po + (PG + q) * PB, xo, d.g_in[q]);
                 }
-                gst<float>(pout + (PF + q) * PB, co * 4, d.df_in[q]);
+                gst<float>(po + (PF + q) * PB, xo, d.df_in[q]);
             }
         }
     }
-    gst<float>(phout, cf * 4, phi);
+    gst<float>(phout, cf, phi);
 }
 
 template <bool FLOW, bool INOUT>
@@ -354,9 +368,13 @@ hipError_t launch_step3(const Dom3& d, const Dom3* d_dev, int par, hipStream_t s
     void* fn = !d.flow ? step_fn<false, false>() : (d.inout ? step_fn<true, true>() : step_fn<true, false>());
     if (!d.flow && d.inout) return hipErrorInvalidValue;
     const int grid = d.nbx * d.nby * d.nbz;
-    int remap = 1;
-    void* args[] = {(void*)&d_dev, (void*)&par, (void*)&remap};
-    return hipLaunchKernel(fn, dim3(grid), dim3(kBlockCells), args, 0, s);
+    void* args[] = {(void*)&d_dev, (void*)&par};
+    // Without flow the registers allow eight workgroups per CU; on lattices beyond the last-level cache five at a
+    // time are faster (256 x 128 x 128: 104.2 us with eight, 98.7 with five, 99.8 with four; 256 x 101 x 110:
+    // 81.3, 73.4, 77.0), so dynamic LDS limits them, as in the 2D step.  With flow the registers allow four.
+    const int64_t bytes = 2 * (int64_t)grid * kBlockCells * (d.npop + 1) * 4;
+    const int pad = !d.flow && bytes > (int64_t(256) << 20) ? 163840 / 5 - 15 * 1024 : 0;
+    return hipLaunchKernel(fn, dim3(grid), dim3(kBlockCells), args, pad, s);
 }
 
 // ------------------------------------------------------------------------------------------ set-up

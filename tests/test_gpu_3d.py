@@ -167,3 +167,12 @@ def test_f4_workload_full_run_against_stored_oracle():
         errs[k] = float(np.abs(got - data[k].astype(np.float64)).max())
         report("F4 full run 2000 steps %s" % k, errs[k])
     assert errs["phi"] <= 1e-4, errs
+
+
+@pytest.mark.parametrize("case", list(CASES))
+@pytest.mark.parametrize("shape", [(64, 16, 4), (65, 17, 3), (66, 2, 5), (130, 35, 6), (67, 51, 2)])
+def test_one_step_across_blocks_and_slabs_3d(case, shape):
+    """The same one-step parity (2e-6, as above: the largest states here have values of the same size) on
+    lattices of several blocks per side: exact blocks, one cell past a block in x and y, rows wrapped
+    narrower and just wider than a staged row, and y slabs of equal and of unequal height."""
+    test_one_step_from_random_state_3d(case, shape)

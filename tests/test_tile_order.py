@@ -1,5 +1,6 @@
-"""The tile order a single lattice's step computes (StepGeom::tile_at) against the plain loops that define it,
-on the host: row order and strips of every width, the last strip narrower or not."""
+"""The tile order a single lattice's step computes (StepGeom::tile_at) and the block order of the 3D step (block_of)
+against the plain loops that define them, on the host: row order and strips of every width, the last strip
+narrower or not; slabs of equal and of unequal height."""
 import os
 import shutil
 import subprocess
@@ -12,6 +13,7 @@ PROGRAM = r"""
 #include <cstdio>
 #include <random>
 #include "snowlb_internal.h"
+#include "snowlb3d_internal.h"
 using namespace snowlb;
 static int check(int ntx, int nty, int W) {
     StepGeom g;
@@ -30,8 +32,33 @@ static int check(int ntx, int nty, int W) {
             }
     return t == g.ntiles ? 0 : 1;
 }
+static int check3(int nbx, int nby, int nbz) {
+    snowlb3d::Dom3 d{};
+    d.nbx = nbx;
+    d.nby = nby;
+    d.nbz = nbz;
+    snowlb3d::set_block_order(d);
+    const int slabs = nby >= 8 ? 8 : 1;
+    int t = 0;
+    for (int s = 0; s < slabs; ++s)
+        for (int k = 0; k < nbz; ++k)
+            for (int j = (int)((int64_t)s * nby / slabs); j < (int)((int64_t)(s + 1) * nby / slabs); ++j)
+                for (int i = 0; i < nbx; ++i, ++t) {
+                    int bx, by, bz;
+                    snowlb3d::block_of(d, t, bx, by, bz);
+                    if (bx != i || by != j || bz != k) {
+                        std::printf("%d x %d x %d block %d\n", nbx, nby, nbz, t);
+                        return 1;
+                    }
+                }
+    return t == nbx * nby * nbz ? 0 : 1;
+}
 int main() {
     int bad = 0;
+    for (int nbx : {1, 2, 3, 4, 8})
+        for (int nby : {1, 2, 7, 8, 9, 15, 16, 17, 51, 64, 67})
+            for (int nbz : {1, 2, 5, 64}) bad += check3(nbx, nby, nbz);
+    bad += check3(1, 32768, 1) + check3(1024, 9, 3) + check3(1, 8, 16384);
     for (int ntx = 1; ntx <= 20; ++ntx)
         for (int nty : {1, 2, 3, 7, 64, 65})
             for (int W = 1; W <= ntx; ++W) bad += check(ntx, nty, W);
