@@ -421,6 +421,16 @@ __global__ void __launch_bounds__(kBlockCells) k_pop_get(DomDesc d, int par, flo
 // (resp. g) resets the rho, j (resp. U) reference planes to 0 -- any consistent reference is valid;
 // populations streamed from the inlet ghost keep the ghost's references.  Writing phi_prev
 // re-encodes h.
+// The 16-bit value of a population p: its deviation is rounded to FP32 and then to 16 bits.  (Left to itself the
+// compiler may fold the conversion into the multiply-add, which rounds once, in some instances and not in
+// others; a written state should not depend on that.)
+template <class S>
+__device__ __forceinline__ typename S::T enc_deviation(float p, float iw, float ref) {
+    float e = __builtin_fmaf(p, iw, -ref);
+    asm("" : "+v"(e));
+    return S::to_ref(e);
+}
+
 template <class S, int SET>
 __global__ void __launch_bounds__(kBlockCells) k_pop_set(DomDesc d, int par, const float* __restrict__ canon) {
     int x, y;
@@ -442,10 +452,12 @@ __global__ void __launch_bounds__(kBlockCells) k_pop_set(DomDesc d, int par, con
         for (int q = 0; q < NQ; ++q) {
             float r[4] = {0.f, 0.f, 0.f, 0.f};
             if (S::kLocalRef && d.inout && x - CX[q] < 0) ref_at<S>(d, par, -1, y - CY[q], r);  // ghost constants
-            if (SET == 0)
-                plane_ptr_w<S>(d, par, q)[i] = f_abs_enc<S>(v[q], q, f_ref(r[R_RHO], r[R_JX], r[R_JY], CX[q], CY[q]));
-            else
-                plane_ptr_w<S>(d, par, d.off_g + q)[i] = S::enc(v[q], IW5[q], g_ref(r[R_U], r[R_JX], r[R_JY], CX[q], CY[q]));
+            const float m = SET == 0 ? f_ref(r[R_RHO], r[R_JX], r[R_JY], CX[q], CY[q])
+                                     : g_ref(r[R_U], r[R_JX], r[R_JY], CX[q], CY[q]);
+            typename S::T e;
+            if constexpr (S::kLocalRef) e = enc_deviation<S>(v[q], SET == 0 ? IW9[q] : IW5[q < 5 ? q : 0], m);
+            else e = SET == 0 ? f_abs_enc<S>(v[q], q, m) : v[q];
+            plane_ptr_w<S>(d, par, (SET == 0 ? 0 : d.off_g) + q)[i] = e;
         }
     } else if constexpr (SET == 2) {
         const float ref = S::kLocalRef ? phip_ptr(d, par)[i1] : 0.f;
