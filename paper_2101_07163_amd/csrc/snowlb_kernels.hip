@@ -49,20 +49,6 @@ __device__ __forceinline__ int wrap_near(int i, int n, int span) {
     return i;
 }
 
-// Closure of the domain for a staged lattice position (gx, gy) that may lie outside it (by less than a staged
-// region, SX x SY): y periodic; x periodic, or (inlet/outlet) the inlet ghost left of x = 0 (returns
-// false) and a copy of column nx-1 right of it.  (sx, sy) receives the position it maps to.
-template <bool INOUT, int SX, int SY>
-__device__ __forceinline__ bool map_pos(int nx, int ny, int gx, int gy, int& sx, int& sy) {
-    sy = wrap_near(gy, ny, SY);
-    if (INOUT) {
-        sx = min(max(gx, 0), nx - 1);
-        return gx >= 0;
-    }
-    sx = wrap_near(gx, nx, SX);
-    return true;
-}
-
 // ---------------------------------------------------------------------------------------------
 // the fused step; RAD is the reach of the gradient stencil (1: E2, E4; 2: E6, E8), i.e. the width of
 // the halo ring staged in LDS
@@ -78,7 +64,7 @@ constexpr int kMinWaves = (RAD == 1 && TY >= 4) ? 4 : 1;
 // 12.5 us, 128^2 without flow 4.0 -> 3.7 us, together with the loads in one block below).
 template <int TX, int TY, class S, bool FLOW, bool INOUT, int RAD, bool LOOP>
 __global__ void __launch_bounds__(TX * TY) __attribute__((amdgpu_waves_per_eu(kMinWaves<TY, RAD>)))
-k_step(const DomDesc* __restrict__ doms, const TileDesc* __restrict__ tiles, int par, int grid, int ntx, int strip,
+k_step(const DomDesc* __restrict__ doms, const TileDesc* __restrict__ tiles, int flags, int grid, int ntx, int strip,
        int per, uint32_t m_per, uint32_t m_strip, uint32_t m_last, uint32_t codes, int ntiles) {
     using T = typename S::T;
     constexpr bool REF = S::kLocalRef;
@@ -88,16 +74,25 @@ k_step(const DomDesc* __restrict__ doms, const TileDesc* __restrict__ tiles, int
     constexpr int RING = LN - NT;
     constexpr int PF = 0, PG = FLOW ? 9 : 0, PH = PG + 5;  // first plane of f, g and h in a copy
     constexpr int NP = (FLOW ? 23 : 14) + (REF ? NR : 0);  // planes per block of a copy (d.nqb)
+    constexpr int PR = FLOW ? 23 : 14;                      // first 16-bit reference plane
     constexpr uint32_t ES = sizeof(T);
+    // Planes follow each other PB bytes apart, so one scalar base in the middle of GP planes reaches all of them with
+    // the 13-bit immediate offsets of the memory instructions; a base per access is two scalar additions each
+    // (FP32 inlet instance: 478 scalar instructions, 292 so; 128^2 without flow 3.7 -> 3.6 us).
+    constexpr int PB = kBlockCells * ES, GP = 8192 / PB, NG = (NP + GP - 1) / GP;
     __shared__ double s_phi[LN];
     __shared__ float s_phif[REF ? LN : 1];  // phi(t) rounded to FP32: the h references
-    __shared__ float s_h[9][LN];
+    __shared__ float s_h[8][LN];            // h_1 .. h_8 (h_0 moves nowhere)
     __shared__ float s_ref[NR][REF ? LN : 1];
+    // A wave of a tile at least 64 cells wide lies in one row: its y and everything made of it is uniform, and an
+    // access is a scalar base (plane and row) plus one of three lane offsets (x, x + 1, x - 1).
+    constexpr bool ROWS = TX % 64 == 0;
+    auto uniform = [](int v) { return ROWS ? __builtin_amdgcn_readfirstlane(v) : v; };
 
     const int tid = threadIdx.x;
-    const int tx = tid % TX, ty = tid / TX;
+    const int tx = tid % TX, ty = uniform(tid / TX);
     const int own = (ty + RAD) * LX + (tx + RAD);
-    const int npar = 1 - par;
+    const int par = flags & 1, npar = 1 - par;
 
     // XCD-aware order: consecutive workgroup ids are spread over the 8 XCDs; give each
     // XCD a contiguous run of tiles so neighbouring tiles share halo lines in that XCD's L2.  XCD x
@@ -110,28 +105,8 @@ k_step(const DomDesc* __restrict__ doms, const TileDesc* __restrict__ tiles, int
     const int xcd = b % 8, kx = b / 8, cnt = G / 8 + (xcd < G % 8 ? 1 : 0);
     const int slot = xcd * (G / 8) + min(xcd, G % 8) + (par ? cnt - 1 - kx : kx);
 
-    // halo position r of the ring: the RAD rows above and below the tile, then RAD columns left and
-    // right of it
-    auto ring_pos = [&](int r, int& lx, int& ly) {
-        if constexpr (RAD == 1) {
-            const bool below = r >= LX, column = r >= 2 * LX, right = r >= 2 * LX + TY;
-            const int kr = below ? r - LX : r, kc = r - 2 * LX - (right ? TY : 0);
-            lx = column ? (right ? LX - 1 : 0) : kr;
-            ly = column ? 1 + kc : (below ? LY - 1 : 0);
-        } else {
-            constexpr int BAND = RAD * LX;
-            if (r < 2 * BAND) {
-                const int k = r < BAND ? r : r - BAND;
-                ly = k / LX + (r < BAND ? 0 : LY - RAD);
-                lx = k % LX;
-            } else {
-                const int k = r - 2 * BAND;
-                const int side = k / (RAD * TY), m = k % (RAD * TY);
-                ly = RAD + m / RAD;
-                lx = (side ? LX - RAD : 0) + m % RAD;
-            }
-        }
-    };
+    // The halo ring: lane tid takes its positions tid, tid + NT, ... (ring_at below).
+    constexpr int RROWS = 2 * RAD * TX, SLOTS = (RING + NT - 1) / NT;
 
     for (int t = slot; !LOOP || t < ntiles; t += G) {
         int dom = 0, x0, y0;
@@ -156,126 +131,160 @@ k_step(const DomDesc* __restrict__ doms, const TileDesc* __restrict__ tiles, int
         }
         const DomDesc& d = doms[dom];
         const int nx = d.nx, ny = d.ny, nbx = d.nbx;
-        // uniform bases: population copies, phi_prev, reference planes
-        const uint64_t pb = (uint64_t)kBlockCells * ES;  // bytes between the planes of a block
-        const uint64_t rb = (uint64_t)kBlockCells * ES;
         const GMEM char* pin = (const GMEM char*)d.pop[par];
         GMEM char* pout = (GMEM char*)d.pop[npar];
         const GMEM char* phin = (const GMEM char*)d.phip[par];
         GMEM char* phout = (GMEM char*)d.phip[npar];
-        const GMEM char* rin = REF ? (const GMEM char*)d.refs[par] : nullptr;
-        GMEM char* rout = REF ? (GMEM char*)d.refs[npar] : nullptr;
 
         const int x = x0 + tx, y = y0 + ty;
         const bool active = (x < nx) && (y < ny);
-        // element offsets of a position in the population buffer (p; the 16-bit reference planes share
-        // its blocks, r = p) and in the phi_prev plane (f)
-        struct Off {
-            uint32_t p, f, r;
+        // byte offsets into the population buffer of a row and of a position in it (the 16-bit reference planes
+        // share its blocks), and into the phi_prev plane
+        auto yof = [&](int sy) { return cell_ypart24(nbx, NP, sy) * ES; };
+        auto xof = [&](int sx) { return cell_xpart(sx, NP) * ES; };
+        auto yof1 = [&](int sy) { return cell_ypart24(nbx, 1, sy) * 4u; };
+        auto xof1 = [&](int sx) { return cell_xpart(sx, 1) * 4u; };
+        // A row of the input copy: its group bases (the row's own offset in them, or, where a wave spans rows, in the
+        // lane's), and the value of plane p at lane offset xo.  The empty asm keeps the compiler from taking
+        // the bases apart again.
+        struct Row {
+            const GMEM char* base[NG];
+            uint32_t lane;
+            __device__ __forceinline__ T get(int p, uint32_t xo) const {
+                return *(const GMEM T*)(base[p / GP] + (lane + xo) + (p % GP - GP / 2) * PB);
+            }
         };
-        auto offs = [&](int sx, int sy) {
-            Off o;
-            o.p = cell_xpart(sx, NP) + cell_ypart24(nbx, NP, sy);
-            o.f = cell_xpart(sx, 1) + cell_ypart24(nbx, 1, sy);
-            o.r = o.p;
-            return o;
+        auto row_of = [&](bool rows, uint32_t yo, int first, int last) {  // of the planes first..last
+            Row r;
+            r.lane = rows ? 0u : yo;
+#pragma unroll
+            for (int g = 0; g < NG; ++g)
+                if (g >= first / GP && g <= last / GP) {
+                    r.base[g] = pin + (rows ? yo : 0u) + (g * GP + GP / 2) * PB;
+                    asm("" : "+s"(r.base[g]));
+                }
+            return r;
         };
-        const uint32_t xp = cell_xpart(x, NP), yp = cell_ypart24(nbx, NP, y);
-        const uint32_t co = xp + yp;  // population offset of this lane's cell (active lanes)
+        auto load1 = [&](bool rows, uint32_t yo, uint32_t xo) {  // phi_prev
+            return rows ? gld<float>(phin + yo, xo) : gld<float>(phin, yo + xo);
+        };
+        // closure of a staged position: y periodic; x periodic, or (inlet/outlet) clamped -- the outlet repeats
+        // column nx - 1, the inlet ghost is masked where it can occur
+        auto cy = [&](int gy) { return wrap_near(gy, ny, LY); };
+        auto cx = [&](int gx) { return INOUT ? min(max(gx, 0), nx - 1) : wrap_near(gx, nx, LX); };
 
         // ---- issue every global load of this tile first: the cell's own h, phi_prev (and 16-bit references), g
-        // and f, which are one contiguous run per workgroup, then the first pass over the halo ring.  The
-        // loads are unconditional (a lane outside the domain, or on the inlet ghost, loads the position the
-        // closure maps it to), so that they form one block and nothing is computed before the last is
-        // issued.  The ring before f and g lets the staging start earlier (1024^2 FP32 30.6 instead of
-        // 30.8 us) but splits the run, which costs HBM-sized lattices 1.8 % (2048^2 149.5 against 146.7 us).
-        // Lanes outside the domain stage the position their LDS slot stands for, which can be the halo of
-        // an active neighbour.
-        T graw[5], fraw[9], hraw[9], rraw[9];
-        T oref[NR], rref[NR];
-        float rphi = 0.f;  // phi_prev of the staged ring position
-        int osx, osy;
-        const bool oreal = map_pos<INOUT, LX, LY>(nx, ny, x, y, osx, osy);  // (x, y) itself for active lanes
-        const Off oo = offs(osx, osy);
-        int rlx = 0, rly = 0;
-        bool rreal = false;
-        const bool has_ring = tid < RING;
+        // and f, which are one contiguous run per workgroup, then the halo ring.  The loads are
+        // unconditional (a lane outside the domain, or on the inlet ghost, loads the position the closure
+        // maps it to), so that they form one block and nothing is computed before the last is issued.  The
+        // ring before f and g lets the staging start earlier (1024^2 FP32 30.6 instead of 30.8 us) but
+        // splits the run, which costs HBM-sized lattices 1.8 % (2048^2 149.5 against 146.7 us); h before g and
+        // f, kept apart from them, is worth 2 % on small lattices (256^2 4.7 -> 4.6 us).  Lanes
+        // outside the domain stage the position their LDS slot stands for, which can be the halo of an
+        // active neighbour.
+        T graw[5], fraw[9], hraw[9], rraw[SLOTS][9];
+        T oref[NR], rref[SLOTS][NR];
+        float rphi[SLOTS];  // phi_prev of the staged ring positions
+        const int osx = cx(x), osy = cy(y);  // (x, y) itself for active lanes
+        const uint32_t xo = xof(osx), yo = yof(osy), xo1 = xof1(osx), yo1 = yof1(osy);
+        const Row own_row = row_of(ROWS, yo, 0, NP - 1);
 #pragma unroll
-        for (int q = 0; q < 9; ++q) hraw[q] = gld<T>(pin + (PH + q) * pb, oo.p * ES);
-        const float ophi = gld<float>(phin, oo.f * 4);
+        for (int q = 0; q < 9; ++q) hraw[q] = own_row.get(PH + q, xo);
+        const float ophi = load1(ROWS, yo1, xo1);
         if (REF) {
 #pragma unroll
-            for (int k = 0; k < NR; ++k) oref[k] = gld<T>(rin + k * rb, oo.r * ES);
+            for (int k = 0; k < NR; ++k) oref[k] = own_row.get(PR + k, xo);
         }
-        uint32_t go = oo.p * ES;
-        asm("" : "+v"(go));  // keeps the 32-bit offset, and with it scalar-base addressing, in this block
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int q = 0; q < 5; ++q) graw[q] = gld<T>(pin + (PG + q) * pb, go);
+        for (int q = 0; q < 5; ++q) graw[q] = own_row.get(PG + q, xo);
+        __builtin_amdgcn_sched_barrier(0);
         if (FLOW) {
 #pragma unroll
-            for (int q = 0; q < 9; ++q) fraw[q] = gld<T>(pin + (PF + q) * pb, go);
+            for (int q = 0; q < 9; ++q) fraw[q] = own_row.get(PF + q, xo);
         }
-        if (has_ring) {
-            ring_pos(tid, rlx, rly);
-            int sx, sy;
-            rreal = map_pos<INOUT, LX, LY>(nx, ny, x0 + rlx - RAD, y0 + rly - RAD, sx, sy);
-            const Off ro = offs(sx, sy);
+        // Ring position r in the staged region.  One cell wide: the rows below and above the tile, corners included,
+        // then the columns.  Two cells wide: the four rows of TX cells, aligned like the tile's own (a wave's
+        // share lies in one row; returns true), then the four columns of LY cells; all passes over it are
+        // loaded here, up front (800^2 E8 16.3 -> 15.2 us).  The aligned form of the narrow ring is slower
+        // (701 x 499 12.9 instead of 12.6 us, 1024^2 30.9 instead of 30.7).
+        auto ring_at = [&](int r, int& lx, int& ly) {
+            if constexpr (RAD == 1) {
+                const bool above = r >= LX, column = r >= 2 * LX, right = r >= 2 * LX + TY;
+                const int kr = above ? r - LX : r, kc = r - 2 * LX - (right ? TY : 0);
+                lx = column ? (right ? LX - 1 : 0) : kr;
+                ly = column ? 1 + kc : (above ? LY - 1 : 0);
+                return false;
+            } else {
+                static_assert(RROWS % 64 == 0 && RROWS + 2 * RAD * LY == RING, "ring");
+                const int k = uniform(r) / TX, c = r - RROWS, col = c / LY;
+                const bool in_rows = uniform(r) < RROWS;
+                ly = in_rows ? (k < RAD ? k : k + TY) : c - col * LY;
+                lx = in_rows ? RAD + r % TX : (col < RAD ? col : col + TX);
+                return ROWS && in_rows;
+            }
+        };
 #pragma unroll
-            for (int q = 0; q < 9; ++q) rraw[q] = gld<T>(pin + (PH + q) * pb, ro.p * ES);
-            if (REF) {
-                rphi = gld<float>(phin, ro.f * 4);
+        for (int sl = 0; sl < SLOTS; ++sl) {
+            const int r = tid + sl * NT;
+            if (r < RING) {
+                int lx, ly;
+                const bool uni = ring_at(r, lx, ly);  // a uniform row: its offset goes to the scalar bases
+                const int sx = cx(x0 + lx - RAD), sy = cy(y0 + ly - RAD);
+                const uint32_t ry = yof(sy), ry1 = yof1(sy);
+                const uint32_t by = uni ? __builtin_amdgcn_readfirstlane(ry) : 0u;
+                const uint32_t by1 = uni ? __builtin_amdgcn_readfirstlane(ry1) : 0u;
+                uint32_t rx = xof(sx) + (uni ? 0u : ry);
+                asm("" : "+v"(rx));
+                const Row row = row_of(true, by, PH, NP - 1);
 #pragma unroll
-                for (int k = 0; k < NR; ++k) rref[k] = gld<T>(rin + k * rb, ro.r * ES);
+                for (int q = 0; q < 9; ++q) rraw[sl][q] = row.get(PH + q, rx);
+                if (REF) {
+                    rphi[sl] = gld<float>(phin + by1, xof1(sx) + (uni ? 0u : ry1));
+#pragma unroll
+                    for (int k = 0; k < NR; ++k) rref[sl][k] = row.get(PR + k, rx);
+                }
             }
         }
         __builtin_amdgcn_sched_barrier(0);
-        // Decode h of one staged position and write phi, h and the 16-bit references to LDS.  phi is
+        // Decode h of one staged position and write phi and the 16-bit references to LDS.  phi is
         // summed in FP64: it is close to -1 or 1 in the bulk, and a gradient of FP32 sums would
         // carry cancellation error of order 1e-7 / |grad phi| into the direction of the normal, i.e.
         // into a and N where |grad phi| is small.  h is stored against its holder's phi_prev.
-        auto stage = [&](bool real, const T raw[9], float href, const T refs[NR], int li, float hh[9]) {
+        auto stage = [&](bool ghost, const T raw[9], float href, const T refs[NR], int li, float hh[9]) {
             double p64 = 0.0;
 #pragma unroll
             for (int q = 0; q < 9; ++q) {
                 hh[q] = S::dec(raw[q], W9[q], href);
                 p64 += (double)hh[q];
-                s_h[q][li] = hh[q];
             }
-            if (INOUT) p64 = real ? p64 : -1.0;  // inlet ghost: phi = -1 (its h are never read)
+            if (INOUT && ghost) p64 = -1.0;  // inlet ghost: phi = -1 (its h are never used)
             s_phi[li] = p64;
             if (REF) {
                 s_phif[li] = (float)p64;
 #pragma unroll
                 for (int k = 0; k < NR; ++k) {
-                    const float ghost = k == R_U ? d.U_in : k == R_RHO ? d.ref_f : k == R_JX ? d.ref_f * d.u_in : 0.f;
-                    s_ref[k][li] = S::from_ref(!INOUT || real ? refs[k] : S::to_ref(ghost));
+                    const float gv = k == R_U ? d.U_in : k == R_RHO ? d.ref_f : k == R_JX ? d.ref_f * d.u_in : 0.f;
+                    s_ref[k][li] = S::from_ref(INOUT && ghost ? S::to_ref(gv) : refs[k]);
                 }
             }
         };
         float h[9];
-        stage(oreal, hraw, ophi, oref, own, h);
-        if (has_ring) {
-            float hr[9];
-            stage(rreal, rraw, rphi, rref, rly * LX + rlx, hr);
-        }
-        // rings larger than the workgroup (e.g. 128 x 2 tiles) take further passes
-        for (int r = tid + NT; r < RING; r += NT) {
-            int lx, ly;
-            ring_pos(r, lx, ly);
-            int sx, sy;
-            const bool real = map_pos<INOUT, LX, LY>(nx, ny, x0 + lx - RAD, y0 + ly - RAD, sx, sy);
-            const Off eo = offs(sx, sy);
-            T raw[9], refs[NR];
-            float pr = 0.f;
+        stage(false, hraw, ophi, oref, own, h);
 #pragma unroll
-            for (int q = 0; q < 9; ++q) raw[q] = gld<T>(pin + (PH + q) * pb, eo.p * ES);
-            if (REF) {
-                pr = gld<float>(phin, eo.f * 4);
+        for (int q = 1; q < 9; ++q) s_h[q - 1][own] = h[q];
 #pragma unroll
-                for (int k = 0; k < NR; ++k) refs[k] = gld<T>(rin + k * rb, eo.r * ES);
+        for (int sl = 0; sl < SLOTS; ++sl) {
+            const int r = tid + sl * NT;
+            if (r < RING) {
+                int lx, ly;
+                ring_at(r, lx, ly);
+                const int li = ly * LX + lx;
+                float hr[9];
+                stage(x0 + lx - RAD < 0, rraw[sl], rphi[sl], rref[sl], li, hr);
+#pragma unroll
+                for (int q = 1; q < 9; ++q) s_h[q - 1][li] = hr[q];
             }
-            float hr[9];
-            stage(real, raw, pr, refs, ly * LX + lx, hr);
         }
         __syncthreads();
 
@@ -502,74 +511,116 @@ k_step(const DomDesc* __restrict__ doms, const TileDesc* __restrict__ tiles, int
                 pair(2, 4, Ny);
                 pair(5, 7, Nx + Ny);
                 pair(6, 8, Ny - Nx);
-                HP[0] = Ka - sum8(HP);
+                // from the rounded Ka in every instance (the compiler would fuse its product into the difference
+                // in some of them)
+                float rest = Ka;
+                asm("" : "+v"(rest));
+                HP[0] = rest - sum8(HP);
             }
 
+            // ---- destination rows y - 1, y, y + 1 of the output copy, as group bases and lane offsets
+            const uint32_t yd[3] = {yof(y > 0 ? y - 1 : ny - 1), yo, yof(y + 1 < ny ? y + 1 : 0)};
+            GMEM char* out[3][NG];
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+#pragma unroll
+                for (int g = 0; g < NG; ++g) {
+                    out[k][g] = pout + (ROWS ? yd[k] : 0u) + (g * GP + GP / 2) * PB;
+                    asm("" : "+s"(out[k][g]));
+                }
+            auto store = [&](int p, int dy, uint32_t xd, T v) {  // plane p, row y + dy, lane offset xd
+                *(GMEM T*)(out[dy + 1][p / GP] + (ROWS ? xd : yd[dy + 1] + xd) + (p % GP - GP / 2) * PB) = v;
+            };
             // ---- references this cell hands to the populations it emits (16-bit storage)
             float rU = 0.f, rR = 0.f, rJx = 0.f, rJy = 0.f;
             if (REF) {
                 const T tU = S::to_ref(U);
-                gst<T>(rout, oo.r * ES, tU);
+                store(PR + R_U, 0, xo, tU);
                 rU = S::from_ref(tU);
                 if (FLOW) {
                     const T tR = S::to_ref(rho), tX = S::to_ref(jx), tY = S::to_ref(jy);
-                    gst<T>(rout + rb, oo.r * ES, tR);
-                    gst<T>(rout + 2 * rb, oo.r * ES, tX);
-                    gst<T>(rout + 3 * rb, oo.r * ES, tY);
+                    store(PR + R_RHO, 0, xo, tR);
+                    store(PR + R_JX, 0, xo, tX);
+                    store(PR + R_JY, 0, xo, tY);
                     rR = S::from_ref(tR);
                     rJx = S::from_ref(tX);
                     rJy = S::from_ref(tY);
                 }
             }
 
-            // ---- push streaming into copy 1 - par (destination offsets: x part + y part)
-            const int yN = (y + 1 < ny) ? y + 1 : 0;
-            const int yS = (y > 0) ? y - 1 : ny - 1;
-            const int xE = (x + 1 < nx) ? x + 1 : (INOUT ? -1 : 0);
-            const int xW = (x > 0) ? x - 1 : (INOUT ? -1 : nx - 1);
-            const uint32_t xpE = cell_xpart(xE < 0 ? 0 : xE, NP), xpW = cell_xpart(xW < 0 ? 0 : xW, NP);
-            const uint32_t ypN = cell_ypart24(nbx, NP, yN), ypS = cell_ypart24(nbx, NP, yS);
-#pragma unroll
-            for (int q = 0; q < 9; ++q) {
-                const int xd = CX[q] > 0 ? xE : (CX[q] < 0 ? xW : x);
-                const uint32_t ypd = CY[q] > 0 ? ypN : (CY[q] < 0 ? ypS : yp);
+            // ---- push streaming into copy 1 - par.  Population q goes to the lane offset xd of row y + c_y, where
+            // h'_q takes h_q of the LDS position li.  On lattices beyond the last-level cache (bit 1 of flags)
+            // FP32 waves pause 6 x 64 cycles before each direction's stores: all stores in one burst hold up the
+            // loads of the CU's other workgroups (64-crystal batch 947 -> 900 us, 3000^2 331 -> 323, 2048^2 151
+            // -> 148.5; pauses of 3 or 4 are worth less, 9 no more; without flow and in 16 bits they only cost).
+            const bool paced = FLOW && !REF && (flags & 2);
+            auto push = [&](int q, uint32_t xd, int li) {
+                if (paced) __builtin_amdgcn_s_sleep(6);
                 const float Pq = __builtin_fmaf(hc, h[q], HP[q]);
-                const int lq = own + CY[q] * LX + CX[q];
-                const float fm = (REF && FLOW) ? f_ref(rR, rJx, rJy, CX[q], CY[q]) : 0.f;
-                const float gm = REF ? (FLOW ? g_ref(rU, rJx, rJy, CX[q], CY[q]) : rU) : 0.f;
-                if (xd >= 0) {
-                    const uint32_t dO = ((CX[q] > 0 ? xpE : (CX[q] < 0 ? xpW : xp)) + ypd) * ES;
-                    const float href = REF ? s_phif[lq] : 0.f;  // h references its holder's phi(t)
-                    gst<T>(pout + (PH + q) * pb, dO, S::enc(Pq - B * s_h[q][lq], IW9[q], href));
-                    if (FLOW) gst<T>(pout + (PF + q) * pb, dO, f_dev_enc<S>(fs[q], q, fm));
-                    if (q < 5) gst<T>(pout + (PG + q) * pb, dO, S::enc(gs[q], IW5[q], gm));
+                const float hat = q == 0 ? h[0] : s_h[q == 0 ? 0 : q - 1][li];
+                const float href = REF ? s_phif[li] : 0.f;  // h references its holder's phi(t)
+                store(PH + q, CY[q], xd, S::enc(__builtin_fmaf(-B, hat, Pq), IW9[q], href));
+                if (FLOW) {
+                    const float fm = REF ? f_ref(rR, rJx, rJy, CX[q], CY[q]) : 0.f;
+                    store(PF + q, CY[q], xd, f_dev_enc<S>(fs[q], q, fm));
                 }
-                if (INOUT) {
-                    if (CX[q] < 0 && x == nx - 1) {
-                        // outlet ghost at x = nx is a copy of this column: it streams into (nx-1, yd)
-                        const uint32_t dO = (xp + ypd) * ES;
-                        const int ld = own + CY[q] * LX;
-                        const float href = REF ? s_phif[ld] : 0.f;
-                        gst<T>(pout + (PH + q) * pb, dO, S::enc(Pq - B * s_h[q][ld], IW9[q], href));
-                        gst<T>(pout + (PF + q) * pb, dO, f_dev_enc<S>(fs[q], q, fm));
-                        if (q < 5) gst<T>(pout + (PG + q) * pb, dO, S::enc(gs[q], IW5[q], gm));
-                    }
-                    if (CX[q] > 0 && x == 0) {
-                        // inlet ghost at x = -1: equilibrium at (rho0, u_in; U_in; phi = -1); its
-                        // reference values are the LDS ones of the ghost column
+                if (q < 5) {
+                    const float gm = REF ? (FLOW ? g_ref(rU, rJx, rJy, CX[q], CY[q]) : rU) : 0.f;
+                    store(PG + q, CY[q], xd, S::enc(gs[q], IW5[q], gm));
+                }
+            };
+            // the directions with the same c_x share a test of the domain's edge and a lane offset (opaque, so
+            // that it stays a 32-bit offset of scalar bases in its block)
+            auto opaque = [](uint32_t v) {
+                asm("" : "+v"(v));
+                return v;
+            };
+            const uint32_t xc = opaque(xo);
+            push(0, xc, own);
+            push(2, xc, own + LX);
+            push(4, xc, own - LX);
+            const bool last = x == nx - 1, first = x == 0;
+            if (!(INOUT && last)) {
+                const uint32_t xe = opaque(xof(last ? 0 : x + 1));
+                push(1, xe, own + 1);
+                push(5, xe, own + LX + 1);
+                push(8, xe, own - LX + 1);
+            }
+            if (!(INOUT && first)) {
+                const uint32_t xw = opaque(xof(first ? nx - 1 : x - 1));
+                push(3, xw, own - 1);
+                push(6, xw, own + LX - 1);
+                push(7, xw, own - LX - 1);
+            }
+            if constexpr (INOUT) {
+                if (last) {
+                    // outlet ghost at x = nx is a copy of this column: it streams into (nx-1, y + cy)
+                    const uint32_t xl = opaque(xo);
+                    push(3, xl, own);
+                    push(6, xl, own + LX);
+                    push(7, xl, own - LX);
+                }
+                if (first) {
+                    // inlet ghost at x = -1: equilibrium at (rho0, u_in; U_in; phi = -1); its reference values
+                    // are the LDS ones of the ghost column
+                    const uint32_t xf = opaque(xo);
+                    auto inflow = [&](int q) {
                         const int lg = own - CX[q] - CY[q] * LX;  // the ghost source in the LDS halo
                         float gfm = 0.f, ggm = 0.f;
-                        if (REF) {
+                        if constexpr (REF) {
                             ggm = g_ref(s_ref[R_U][lg], s_ref[R_JX][lg], s_ref[R_JY][lg], CX[q], CY[q]);
                             gfm = f_ref(s_ref[R_RHO][lg], s_ref[R_JX][lg], s_ref[R_JY][lg], CX[q], CY[q]);
                         }
-                        gst<T>(pout + (PH + q) * pb, co * ES, S::enc(-W9[q], IW9[q], REF ? phi : 0.f));
-                        gst<T>(pout + (PF + q) * pb, co * ES, f_dev_enc<S>(d.df_in[q], q, gfm));
-                        if (q < 5) gst<T>(pout + (PG + q) * pb, co * ES, S::enc(d.g_in[q], IW5[q], ggm));
-                    }
+                        store(PH + q, 0, xf, S::enc(-W9[q], IW9[q], REF ? phi : 0.f));
+                        store(PF + q, 0, xf, f_dev_enc<S>(d.df_in[q], q, gfm));
+                        if (q < 5) store(PG + q, 0, xf, S::enc(d.g_in[q], IW5[q], ggm));
+                    };
+                    inflow(1);
+                    inflow(5);
+                    inflow(8);
                 }
             }
-            gst<float>(phout, oo.f * 4, phi);
+            gst<float>(phout + (ROWS ? yo1 : 0u), opaque(xo1 + (ROWS ? 0u : yo1)), phi);
         }
         if (!LOOP) break;
         __syncthreads();  // LDS is reused by the next tile
@@ -636,15 +687,18 @@ static void* step_kernel(int cfg, int storage, int flow, int inout, int rad, boo
     return nullptr;
 }
 
-// Dynamic LDS that limits the workgroups per CU of an FP32 step whose lattices do not fit in the last-level cache
-// to 20 waves.  The kernel's registers allow 28, and lattices in that cache are fastest with them (1024^2 30.8
-// against 31.3 us, 701 x 499 12.8 against 13.8 us), but from HBM so many tiles in flight cost more than they
-// hide: 2048^2 156.8 us without the limit, 148.0 at 16 waves, 146.8 at 20; 3000^2 351.9, 324.7, 325.0; without
-// flow 2048^2 99.9, 93.3, 93.5.  16-bit storage keeps them all (2048^2 FP16 100.1 against 101.3 us).
-static int step_lds_pad(int cfg, int rad) {
+// Dynamic LDS that limits the waves per CU of an FP32 step whose lattices do not fit in the last-level cache: to 20
+// with flow, 16 without.  The registers allow 28 to 32, and lattices in that cache are fastest with them (1024^2
+// 30.7 us, 32.4 with 12; 701 x 499 12.6 and 14.5), but from HBM more tiles in flight than the L2 holds (4 MB per
+// XCD, 47 KB per tile with flow) evict halo and partly written lines: 2048^2 with flow reads 9 % and writes 4 %
+// more than with the limit and takes 159 us instead of 148 to 149 (3000^2 359 and 323; 12 waves 321, but the
+// 64-crystal batch 960 instead of 900); without flow 2048^2 96.9, 92.9 with 16, 112.7 with 12.  16-bit storage
+// (29 KB per tile) keeps them all (2048^2 FP16 99.1 us, 96.9 to 100.5 with 16 to 20 waves, 126.8 with 12; 1024^2
+// 21.7, 23.7 with 16).
+static int step_lds_pad(int cfg, int flow, int rad) {
     const TileCfg& t = kTiles[cfg];
-    const int waves = t.tx * t.ty / 64, used = (t.tx + 2 * rad) * (t.ty + 2 * rad) * 44 + 256;
-    return std::max(0, std::min(65536, 163840 * waves / 20) - used);
+    const int limit = flow ? 20 : 16, waves = t.tx * t.ty / 64, used = (t.tx + 2 * rad) * (t.ty + 2 * rad) * 40 + 256;
+    return std::max(0, std::min(65536, 163840 * waves / limit) - used);
 }
 
 // Grid of a step launch.  grid_mode 0: one workgroup per tile, dispatched in (XCD-contiguous) tile
@@ -676,9 +730,10 @@ hipError_t launch_step(int cfg, int storage, int flow, int inout, int rad, const
     if (geom.ntiles <= 0) return hipSuccess;
     const int nt = kTiles[cfg].tx * kTiles[cfg].ty;
     StepGeom g = geom;
-    void* args[] = {(void*)&doms_dev, (void*)&tiles_dev, (void*)&par, (void*)&g.grid, (void*)&g.ntx, (void*)&g.strip,
+    int flags = par | (from_hbm ? 2 : 0);
+    void* args[] = {(void*)&doms_dev, (void*)&tiles_dev, (void*)&flags, (void*)&g.grid, (void*)&g.ntx, (void*)&g.strip,
                     (void*)&g.per, (void*)&g.m_per, (void*)&g.m_strip, (void*)&g.m_last, (void*)&g.codes, (void*)&g.ntiles};
-    const int pad = storage == 0 && from_hbm ? step_lds_pad(cfg, rad) : 0;
+    const int pad = storage == 0 && from_hbm ? step_lds_pad(cfg, flow, rad) : 0;
     return hipLaunchKernel(fn, dim3(g.grid), dim3(nt), args, pad, s);
 }
 
