@@ -28,8 +28,8 @@
  *   SNOWLB_TUNE_STEPS      steps per timing sample of the autotuner (default 20, even)
  *   SNOWLB_BUFFER_STAGGER  bytes added after each 64 KiB-padded buffer of a lattice so that the
  *                          buffers a tile touches start on different HBM channels (default 2304)
- *   SNOWLB_GRAPH_STEPS     steps per captured graph of snowlb_step (default 32, even); fewer steps
- *                          than that are replayed from a captured two-step graph
+ *   SNOWLB_GRAPH_STEPS     steps per captured graph of snowlb_step (default 32, even); calls of fewer
+ *                          than eight graphs' steps, and the rest of longer ones, are launched directly
  *   SNOWLB_NO_GRAPH        1: launch every step directly instead of replaying graphs
  *   SNOWLB_ADJ_OVERLAP     0: run the adjoint backward pass in serial order on the caller's stream
  *                          (default 1: recompute the next checkpoint interval on a second stream of
@@ -226,12 +226,15 @@ int32_t snowlb_get_grid_mode(const snowlb_ctx* ctx);
  * EUNSUPPORTED otherwise).
  *
  * snowlb_adj_forward runs n >= 1 steps from the current state (normally right after snowlb_init),
- * keeping a checkpoint of the state every ckpt_stride steps (0: ceil(sqrt(n))); afterwards the
- * context holds phi_T (read it with snowlb_read).  snowlb_adj_backward then takes dL/dphi_T
+ * keeping a checkpoint of the state every ckpt_stride steps (0: ceil(sqrt(n)), or every state while
+ * the n states take at most 16 GiB and half of the free device memory); afterwards the context holds
+ * phi_T (read it with snowlb_read).  snowlb_adj_backward then takes dL/dphi_T
  * (ny x nx device field) for any loss L(phi_T) and returns, by the hand-written reverse of each step
  * with the states recomputed from the checkpoints: dL/dU_init (ny x nx device field, the gradient
  * with respect to the initial supersaturation field), dL/deps and dL/dU0 = sum dL/dU_init (host
- * doubles, reduced in FP64 in a fixed order).  Memory: about (n/stride + 2 stride) state copies.
+ * doubles, reduced in FP64 in a fixed order).  Memory: about (n/stride + 2 stride) state copies, or n
+ * when every state is kept (nothing is then recomputed, and the results are bitwise the same); it
+ * belongs to the context and is reused by later calls.
  * The backward may be called several times after one forward (different dL/dphi_T).  It recomputes
  * checkpoint intervals on a second stream that the context owns (see SNOWLB_ADJ_OVERLAP), ordered
  * after all work queued on `stream` before the call; it returns when the work of both is done. */

@@ -217,6 +217,8 @@ __global__ void __launch_bounds__(ANT) k_adj(AdjDesc A) {
     const GMEM char* st = (const GMEM char*)A.st;
     const GMEM char* lin = (const GMEM char*)A.lin;
     GMEM char* lout = (GMEM char*)A.lout;
+    // this workgroup's eps partial of the later steps, loaded here rather than at the very end
+    const double epart = tid == 0 ? A.epart[blockIdx.x] : 0.0;
 
     // ---- global loads before the barrier: what pass A on the tile needs.  Values used only later
     // (the ring's inputs, lambda_h(t + 1) of the cell itself for pass B) are loaded where they are
@@ -318,7 +320,7 @@ __global__ void __launch_bounds__(ANT) k_adj(AdjDesc A) {
     if (tid == 0) {
         double t = 0.0;
         for (int k = 0; k < ANT / 64; ++k) t += s_red[k];
-        A.epart[blockIdx.x] += t;
+        A.epart[blockIdx.x] = epart + t;
     }
 }
 
@@ -354,18 +356,18 @@ __global__ void __launch_bounds__(256) k_adj_uinit(AdjDesc A, float* __restrict_
     if (tid == 0) rows[y] = (s_red[0] + s_red[1]) + (s_red[2] + s_red[3]);
 }
 
-// out[0] = sum of the eps partials, out[1] = sum of the row sums; fixed order
-__global__ void __launch_bounds__(64) k_adj_final(const double* __restrict__ epart, int ne,
-                                                  const double* __restrict__ rows, int nr, double* __restrict__ out) {
-    if (threadIdx.x == 0) {
-        double e = 0.0;
-        for (int k = 0; k < ne; ++k) e += epart[k];
-        out[0] = e;
-    } else if (threadIdx.x == 1) {
-        double u = 0.0;
-        for (int k = 0; k < nr; ++k) u += rows[k];
-        out[1] = u;
-    }
+// out[0] = sum of the eps partials, out[1] = sum of the row sums: a wave for each, lane l adding the values l, l + 64,
+// ... in order, then a tree over the lanes -- a fixed order (one lane for all values took 43 us at 512^2).
+__global__ void __launch_bounds__(128) k_adj_final(const double* __restrict__ epart, int ne,
+                                                   const double* __restrict__ rows, int nr, double* __restrict__ out) {
+    const int which = threadIdx.x / 64, lane = threadIdx.x % 64;
+    const double* v = which == 0 ? epart : rows;
+    const int n = which == 0 ? ne : nr;
+    double t = 0.0;
+#pragma unroll 4
+    for (int k = lane; k < n; k += 64) t += v[k];
+    t = wave_sum_d(t);
+    if (lane == 0) out[which] = t;
 }
 
 int adj_blocks(const AdjDesc& A) { return ((A.nx + ATX - 1) / ATX) * ((A.ny + ATY - 1) / ATY); }
@@ -384,7 +386,7 @@ hipError_t launch_adj_finish(const AdjDesc& A, float* dU, double* rows, double* 
     hipLaunchKernelGGL(k_adj_uinit, dim3(A.ny), dim3(256), 0, s, A, dU, rows);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_adj_final, dim3(1), dim3(64), 0, s, A.epart, adj_blocks(A), rows, A.ny, out);
+    hipLaunchKernelGGL(k_adj_final, dim3(1), dim3(128), 0, s, A.epart, adj_blocks(A), rows, A.ny, out);
     return hipGetLastError();
 }
 

@@ -74,11 +74,11 @@ struct Driver {
     int par = 0;
     int64_t step = 0;
     hipStream_t cap_stream = nullptr;
-    // captured step loops: [0] K steps, [1] two steps (the remainder below K), each starting from copy 0
+    // captured loop of K steps, starting from copy 0
     struct StepGraph {
         hipGraphExec_t exec = nullptr;
         int steps = 0, tile = -1, mode = -1;
-    } graphs[2];
+    } graph;
     std::string err;
 
     ~Driver() { release(); }
@@ -113,10 +113,8 @@ struct Driver {
     }
 
     void drop_graph() {
-        for (StepGraph& g : graphs) {
-            if (g.exec) (void)hipGraphExecDestroy(g.exec);
-            g = StepGraph{};
-        }
+        if (graph.exec) (void)hipGraphExecDestroy(graph.exec);
+        graph = StepGraph{};
     }
 
     static int list_index(int cfg, int mode) { return kTileOrders * cfg + (mode >> 1); }
@@ -189,10 +187,10 @@ struct Driver {
         return SNOWLB_OK;
     }
 
-    // Capture K steps (K even, starting from copy 0) into graph slot `which`, unless it already holds
-    // them for the current tile configuration and grid mode.
-    snowlb_status ensure_graph(int which, int K) {
-        StepGraph& G = graphs[which];
+    // Capture K steps (K even, starting from copy 0), unless the graph already holds them for the current
+    // tile configuration and grid mode.
+    snowlb_status ensure_graph(int K) {
+        StepGraph& G = graph;
         if (G.exec && G.steps == K && G.tile == tile && G.mode == grid_mode) return SNOWLB_OK;
         if (G.exec) (void)hipGraphExecDestroy(G.exec);
         G = StepGraph{};
@@ -222,35 +220,28 @@ struct Driver {
         return SNOWLB_OK;
     }
 
-    snowlb_status replay(int which, int K, hipStream_t s) {
-        hipError_t e = hipGraphLaunch(graphs[which].exec, s);
-        if (e != hipSuccess) return hipfail(e, "hipGraphLaunch");
-        step += K;
-        return SNOWLB_OK;
-    }
-
-    // n steps with the current configuration, replayed from captured graphs: one single launch first
-    // if the state sits in copy 1 (the graphs start from copy 0), then whole graphs of K steps while
-    // at least K remain, then graphs of two steps, and a single launch for an odd last step.
+    // n steps with the current configuration.  Calls of fewer than kGraphRuns graphs' steps are launched directly:
+    // a direct launch costs the host 2.8 us, less than the smallest step, and steps follow each other a
+    // little faster than inside a graph (128^2 3.4 us against 3.5, 512^2 6.2 against 6.4), while a graph has to
+    // be captured first and short graphs for a remainder leave gaps between them (50 steps of 128^2: 237 us
+    // as one graph of 32 and nine of two).  Long calls replay graphs of K steps, which leave the host free
+    // (1.1 us a step), after one direct launch if the state sits in copy 1 (the graph starts from copy 0).
+    static constexpr int kGraphRuns = 8;
     snowlb_status run(int n, hipStream_t s) {
         snowlb_status st = ensure_tiles(tile, grid_mode);
         if (st) return st;
         const int K = std::max(2, env_int("SNOWLB_GRAPH_STEPS", 32) & ~1);
-        if (env_int("SNOWLB_NO_GRAPH", 0)) return plain(tile, grid_mode, n, s);
-        if (par == 1 && n > 0) {
-            st = plain(tile, grid_mode, 1, s);
-            if (st) return st;
-            n -= 1;
-        }
-        if (n >= K) {
-            if ((st = ensure_graph(0, K))) return st;
-            for (; n >= K; n -= K)
-                if ((st = replay(0, K, s))) return st;
-        }
-        if (n >= 2) {
-            if ((st = ensure_graph(1, 2))) return st;
-            for (; n >= 2; n -= 2)
-                if ((st = replay(1, 2, s))) return st;
+        if (n / K >= kGraphRuns && !env_int("SNOWLB_NO_GRAPH", 0)) {
+            if (par == 1) {
+                if ((st = plain(tile, grid_mode, 1, s))) return st;
+                n -= 1;
+            }
+            if ((st = ensure_graph(K))) return st;
+            for (; n >= K; n -= K) {
+                const hipError_t e = hipGraphLaunch(graph.exec, s);
+                if (e != hipSuccess) return hipfail(e, "hipGraphLaunch");
+                step += K;
+            }
         }
         return plain(tile, grid_mode, n, s);
     }
@@ -440,13 +431,18 @@ struct snowlb_ctx {
         int64_t slot_bytes = 0, nslots = 0;
         int n = 0, stride = 0, nck = 0;
         bool have_forward = false;
+        bool tape = false;     // the slots hold every state t = 0..n-1 of the forward pass (else checkpoints)
+        float tape_eps = 0.f;  // eps the tape between its checkpoints was computed with
         float* buf = nullptr;  // lambda[0], lambda[1] (15 planes each)
         double* epart = nullptr;
         double* rows = nullptr;
         double* d_out = nullptr;
         double* h_out = nullptr;  // pinned, 2 doubles
-        DomDesc* d_segdoms = nullptr;  // two segment areas of (stride - 1) step descriptors each
-        int nsegdoms = 0;
+        // step descriptors: of the two segment areas, of the tape, and of the forward pass's last step, which
+        // writes the context's copy 0; and what of them is on the device
+        DomDesc* d_segdoms = nullptr;
+        DomDesc segdoms[4];
+        bool segdoms_valid = false;
         // the backward pass recomputes the next interval on its own stream while the current one is
         // reversed; events order the two (index: segment area)
         hipStream_t rstream = nullptr;
@@ -604,7 +600,7 @@ void adj_free(snowlb_ctx* c) {
     if (c->adj.rstream) (void)hipStreamDestroy(c->adj.rstream);
     c->adj.rstream = nullptr;
     c->adj.nslots = 0;
-    c->adj.nsegdoms = 0;
+    c->adj.segdoms_valid = false;
     c->adj.have_forward = false;
 }
 
@@ -975,6 +971,77 @@ static char* adj_slot(snowlb_ctx* c, int64_t k) { return (char*)c->adj.slots + k
 // cells of the lattice padded to whole 64 x 4 blocks (the size of one plane of the cell order)
 static int64_t adj_cells(const snowlb_ctx* c) { return (int64_t)c->dom.nbx * kBlockX * round_up(c->p.ny, kBlockY); }
 
+// First slot of segment area a (two areas of `stride` states follow the checkpoints).
+static int64_t adj_area_slot(const snowlb_ctx* c, int a) { return (int64_t)c->adj.nck + (int64_t)a * c->adj.stride; }
+
+// Slots for `need` states: kept from an earlier call if there are enough.
+static snowlb_status adj_slots(snowlb_ctx* c, int64_t need, int64_t slot_bytes) {
+    if (c->adj.nslots >= need && c->adj.slot_bytes == slot_bytes) return SNOWLB_OK;
+    adj_drop_graphs(c);  // their kernels bake the slots in
+    if (c->adj.slots) (void)hipFree(c->adj.slots);
+    c->adj.slots = nullptr;
+    c->adj.nslots = 0;
+    HIPCHK(c, hipMalloc(&c->adj.slots, (size_t)(need * slot_bytes)));
+    c->adj.nslots = need;
+    c->adj.slot_bytes = slot_bytes;
+    return SNOWLB_OK;
+}
+
+// Whether the forward pass keeps every state: the caller left the checkpoint stride to the library, and the states
+// fit in kTapeBytes and in half of the memory that is free (or are there from an earlier call).
+constexpr int64_t kTapeBytes = int64_t(16) << 30;
+static bool adj_tape_fits(const snowlb_ctx* c, int n, int stride, int64_t slot_bytes) {
+    if (stride > 0 || (int64_t)n * slot_bytes > kTapeBytes) return false;
+    if (c->adj.nslots >= n && c->adj.slot_bytes == slot_bytes) return true;
+    size_t free_bytes = 0, total = 0;
+    if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) return false;
+    return (int64_t)n * slot_bytes <= (int64_t)(free_bytes / 2);
+}
+
+// The step descriptors from the context's current domain (eps may have changed) and slot layout: step i of a
+// segment area or of the tape reads slot i of it and writes slot i + 1.  They are uploaded only when they
+// differ from those on the device, once nothing queued can read them any more.
+static snowlb_status adj_descriptors(snowlb_ctx* c) {
+    DomDesc h[4];
+    std::memset((void*)h, 0, sizeof h);  // padding too: they are compared as bytes
+    auto set = [&](int k, char* from, char* to) {
+        std::memcpy((void*)&h[k], (const void*)&c->dom, sizeof(DomDesc));
+        h[k].pop[0] = from;
+        h[k].pop[1] = to;
+        h[k].phip[0] = (float*)(from + c->pop_bytes);
+        h[k].phip[1] = (float*)(to + c->pop_bytes);
+        h[k].slot_stride = c->adj.slot_bytes;
+    };
+    if (c->adj.tape) {
+        set(2, adj_slot(c, 0), adj_slot(c, 1));
+        set(3, adj_slot(c, c->adj.n - 1), adj_slot(c, 0));
+        h[3].pop[1] = c->dom.pop[0];
+        h[3].phip[1] = c->dom.phip[0];
+        h[3].slot_stride = 0;
+    } else {
+        for (int ar = 0; ar < 2; ++ar) set(ar, adj_slot(c, adj_area_slot(c, ar)), adj_slot(c, adj_area_slot(c, ar) + 1));
+    }
+    if (c->adj.segdoms_valid && std::memcmp((const void*)h, (const void*)c->adj.segdoms, sizeof h) == 0) return SNOWLB_OK;
+    c->adj.segdoms_valid = false;
+    HIPCHK(c, hipDeviceSynchronize());
+    if (!c->adj.d_segdoms) HIPCHK(c, hipMalloc(&c->adj.d_segdoms, sizeof h));
+    HIPCHK(c, hipMemcpy(c->adj.d_segdoms, h, sizeof h, hipMemcpyHostToDevice));
+    std::memcpy((void*)c->adj.segdoms, (const void*)h, sizeof h);
+    c->adj.segdoms_valid = true;
+    return SNOWLB_OK;
+}
+
+// Steps first..last-1 of the tape: from slot i to slot i + 1.
+static snowlb_status adj_tape_steps(snowlb_ctx* c, int first, int last, hipStream_t s) {
+    Driver& D = c->drv;
+    const StepGeom sg = D.geom(D.tile, D.grid_mode);
+    for (int i = first; i < last; ++i) {
+        const hipError_t e = launch_step(D.tile, c->p.storage, 0, 0, 1, c->adj.d_segdoms + 2, nullptr, sg, D.from_hbm, 0, s, i);
+        if (e != hipSuccess) return hip_fail(c, e, "adjoint tape step");
+    }
+    return SNOWLB_OK;
+}
+
 snowlb_status snowlb_adj_forward(snowlb_ctx* c, int32_t n, int32_t stride, void* stream) {
     if (!c) return SNOWLB_EINVAL;
     if (snowlb_status st = adj_check(c)) return st;
@@ -984,33 +1051,46 @@ snowlb_status snowlb_adj_forward(snowlb_ctx* c, int32_t n, int32_t stride, void*
     const int st = stride > 0 ? stride : (int)std::ceil(std::sqrt((double)n));
     const int nck = (n + st - 1) / st;
     const int64_t slot_bytes = c->pop_bytes + c->phip_bytes;
-    const int64_t need = (int64_t)nck + 2 * (int64_t)st;  // checkpoints, then two segment areas
-    if (c->adj.nslots < need || c->adj.slot_bytes != slot_bytes) {
-        if (c->adj.slots) (void)hipFree(c->adj.slots);
-        c->adj.slots = nullptr;
-        c->adj.nslots = 0;
-        HIPCHK(c, hipMalloc(&c->adj.slots, (size_t)(need * slot_bytes)));
-        c->adj.nslots = need;
-        c->adj.slot_bytes = slot_bytes;
-        c->adj.nsegdoms = 0;  // segment descriptors point into the slots
-    }
+    c->adj.have_forward = false;
     c->adj.n = n;
     c->adj.stride = st;
     c->adj.nck = nck;
-    for (int k = 0; k < nck; ++k) {
-        char* sl = adj_slot(c, k);
+    c->adj.tape = adj_tape_fits(c, n, stride, slot_bytes) && adj_slots(c, n, slot_bytes) == SNOWLB_OK;
+    if (!c->adj.tape) {
+        (void)hipGetLastError();  // of a tape that could not be allocated
+        // checkpoints, then two segment areas
+        if (snowlb_status r = adj_slots(c, (int64_t)nck + 2 * (int64_t)st, slot_bytes)) return r;
+    }
+    if (snowlb_status r = from_driver(c, c->drv.ensure_tiles(c->drv.tile, c->drv.grid_mode))) return r;
+    if (snowlb_status r = adj_descriptors(c)) return r;
+    auto keep = [&](int64_t slot) -> snowlb_status {
+        char* sl = adj_slot(c, slot);
         HIPCHK(c, hipMemcpyAsync(sl, c->dom.pop[c->drv.par], c->pop_bytes, hipMemcpyDeviceToDevice, s));
         HIPCHK(c, hipMemcpyAsync(sl + c->pop_bytes, c->dom.phip[c->drv.par], c->phip_bytes, hipMemcpyDeviceToDevice, s));
-        const int len = std::min(st, n - k * st);
-        snowlb_status r = from_driver(c, c->drv.run(len, s));
-        if (r) return r;
+        return SNOWLB_OK;
+    };
+    if (c->adj.tape) {
+        // Every state is kept where its step writes it, so the backward pass recomputes nothing and neither pass
+        // copies checkpoints (512^2, 100 steps, both passes: 3.0 -> 2.0 ms).
+        c->adj.tape_eps = c->dom.eps;
+        if (snowlb_status r = keep(0)) return r;
+        if (snowlb_status r = adj_tape_steps(c, 0, n - 1, s)) return r;
+        Driver& D = c->drv;
+        const hipError_t e = launch_step(D.tile, c->p.storage, 0, 0, 1, c->adj.d_segdoms + 3, nullptr,
+                                         D.geom(D.tile, D.grid_mode), D.from_hbm, 0, s);
+        if (e != hipSuccess) return hip_fail(c, e, "adjoint tape step");
+        D.par = 0;
+        D.step += n;
+    } else {
+        for (int k = 0; k < nck; ++k) {
+            if (snowlb_status r = keep(k)) return r;
+            const int len = std::min(st, n - k * st);
+            if (snowlb_status r = from_driver(c, c->drv.run(len, s))) return r;
+        }
     }
     c->adj.have_forward = true;
     return SNOWLB_OK;
 }
-
-// First slot of segment area a (two areas of `stride` states follow the checkpoints).
-static int64_t adj_area_slot(const snowlb_ctx* c, int a) { return (int64_t)c->adj.nck + (int64_t)a * c->adj.stride; }
 
 // Captured programs of one checkpoint interval of length len in segment area `area`: kind 0, the
 // (len - 1) recompute steps from the checkpoint copied into the area's first slot; kind 1, the len
@@ -1059,10 +1139,9 @@ static snowlb_status adj_graph(snowlb_ctx* c, int kind, AdjDesc A, float* const 
     HIPCHK(c, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
     hipError_t le = hipSuccess;
     if (kind == 0) {
-        const DomDesc* sd = c->adj.d_segdoms + (int64_t)area * std::max(c->adj.stride - 1, 1);
         const StepGeom sg = D.geom(D.tile, D.grid_mode);
         for (int i = 0; i + 1 < len && le == hipSuccess; ++i)
-            le = launch_step(D.tile, c->p.storage, 0, 0, 1, sd + i, nullptr, sg, D.from_hbm, 0, cs);
+            le = launch_step(D.tile, c->p.storage, 0, 0, 1, c->adj.d_segdoms + area, nullptr, sg, D.from_hbm, 0, cs, i);
     } else {
         const int64_t base = adj_area_slot(c, area);
         for (int i = len - 1; i >= 0 && le == hipSuccess; --i) {
@@ -1126,35 +1205,7 @@ snowlb_status snowlb_adj_backward(snowlb_ctx* c, const float* dphi, float* dU, d
         HIPCHK(c, hipHostMalloc(&c->adj.h_out, 2 * sizeof(double), hipHostMallocDefault));
     }
     const int st = c->adj.stride, n = c->adj.n;
-    const int per_area = std::max(st - 1, 1);
-    {
-        // Step i of a recompute in area `ar` reads slot i of the area and writes slot i + 1.  The
-        // descriptors are rebuilt on every call from the context's current domain (eps may have
-        // changed since the forward pass through snowlb_set_eps) and the current slot layout (the
-        // segment areas follow the checkpoints, so they move when the checkpoint count changes).
-        std::vector<DomDesc> h((size_t)(2 * per_area), c->dom);
-        for (int ar = 0; ar < 2; ++ar)
-            for (int i = 0; i + 1 < st; ++i) {
-                DomDesc& d = h[(size_t)(ar * per_area + i)];
-                char* a = adj_slot(c, adj_area_slot(c, ar) + i);
-                char* b = adj_slot(c, adj_area_slot(c, ar) + i + 1);
-                d.pop[0] = a;
-                d.pop[1] = b;
-                d.phip[0] = (float*)(a + c->pop_bytes);
-                d.phip[1] = (float*)(b + c->pop_bytes);
-            }
-        if (c->adj.nsegdoms < (int)h.size()) {
-            if (c->adj.d_segdoms) (void)hipFree(c->adj.d_segdoms);
-            c->adj.d_segdoms = nullptr;
-            c->adj.nsegdoms = 0;
-            HIPCHK(c, hipMalloc(&c->adj.d_segdoms, h.size() * sizeof(DomDesc)));
-            c->adj.nsegdoms = (int)h.size();
-        }
-        // the previous backward pass returned only after all of its work (both streams) was done,
-        // so once the caller's stream has drained nothing reads the descriptors any more
-        HIPCHK(c, hipStreamSynchronize(s));
-        HIPCHK(c, hipMemcpy(c->adj.d_segdoms, h.data(), h.size() * sizeof(DomDesc), hipMemcpyHostToDevice));
-    }
+    if (snowlb_status r2 = adj_descriptors(c)) return r2;
     float* lam[2] = {c->adj.buf, c->adj.buf + (kAdjPlanes + 1) * cells};
     A.epart = c->adj.epart;
     HIPCHK(c, hipMemsetAsync(c->adj.epart, 0, (size_t)nblk * sizeof(double), s));
@@ -1165,6 +1216,37 @@ snowlb_status snowlb_adj_backward(snowlb_ctx* c, const float* dphi, float* dU, d
     Driver& D = c->drv;
     snowlb_status r = from_driver(c, D.ensure_tiles(D.tile, D.grid_mode));
     if (r) return r;
+    int cur = 0;
+    auto finish = [&]() -> snowlb_status {
+        A.lin = lam[cur];
+        e = launch_adj_finish(A, dU, c->adj.rows, c->adj.d_out, s);
+        if (e != hipSuccess) return hip_fail(c, e, "adjoint reduction kernels");
+        HIPCHK(c, hipMemcpyAsync(c->adj.h_out, c->adj.d_out, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
+        HIPCHK(c, hipStreamSynchronize(s));
+        *deps = c->adj.h_out[0];
+        *dU0 = c->adj.h_out[1];
+        return SNOWLB_OK;
+    };
+    if (c->adj.tape) {
+        // The states are the ones a recomputation from the checkpoints would give; after a change of eps they are
+        // recomputed, checkpoint interval by interval, in place.
+        if (c->adj.tape_eps != c->dom.eps) {
+            for (int k = 0; k < c->adj.nck; ++k)
+                if (snowlb_status r2 = adj_tape_steps(c, k * st, std::min(k * st + st, n) - 1, s)) return r2;
+            c->adj.tape_eps = c->dom.eps;
+        }
+        for (int i = n - 1; i >= 0; --i) {
+            A.st = (const float*)adj_slot(c, i);
+            A.lin = lam[cur];
+            A.lout = lam[1 - cur];
+            A.lppin = lam[cur] + kAdjPlanes * cells;
+            A.lppout = lam[1 - cur] + kAdjPlanes * cells;
+            e = launch_adj_step(A, s);
+            if (e != hipSuccess) return hip_fail(c, e, "adjoint step kernel");
+            cur ^= 1;
+        }
+        return finish();
+    }
     // Checkpoint intervals are reversed from the last to the first.  Interval k lives in segment area
     // k % 2: its checkpoint is copied into the area's first slot, (len - 1) recompute steps fill the
     // rest, and len reverse steps consume it.  With overlap (the default), interval k - 1 is
@@ -1197,7 +1279,6 @@ snowlb_status snowlb_adj_backward(snowlb_ctx* c, const float* dphi, float* dU, d
         HIPCHK(c, hipStreamWaitEvent(rs, c->adj.ev_start, 0));
     }
     if (snowlb_status r2 = recompute(c->adj.nck - 1)) return r2;
-    int cur = 0;
     for (int k = c->adj.nck - 1; k >= 0; --k) {
         const int len = std::min(st, n - k * st), ar = k & 1;
         if (overlap) HIPCHK(c, hipStreamWaitEvent(s, c->adj.ev_rec[ar], 0));
@@ -1212,14 +1293,7 @@ snowlb_status snowlb_adj_backward(snowlb_ctx* c, const float* dphi, float* dU, d
             if (snowlb_status r2 = recompute(k - 1)) return r2;
         }
     }
-    A.lin = lam[cur];
-    e = launch_adj_finish(A, dU, c->adj.rows, c->adj.d_out, s);
-    if (e != hipSuccess) return hip_fail(c, e, "adjoint reduction kernels");
-    HIPCHK(c, hipMemcpyAsync(c->adj.h_out, c->adj.d_out, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
-    HIPCHK(c, hipStreamSynchronize(s));
-    *deps = c->adj.h_out[0];
-    *dU0 = c->adj.h_out[1];
-    return SNOWLB_OK;
+    return finish();
 }
 
 // ---------------------------------------------------------------------------------------------- batch

@@ -88,6 +88,8 @@ struct DomDesc {
                         // 0: q = (1 - phi)/2 clamped to [0, 1]
     int32_t stencil;    // isotropic gradient: 2, 4 (one-cell reach) or 6, 8 (two-cell reach)
     float tauf_m_half;  // tau_f - 1/2 (= guo / omega_f)
+    int64_t slot_stride;  // bytes from the copies of step k of a launch to those of step k + 1 (the states of an
+                          // adjoint tape follow each other in memory); 0 for two copies that alternate
     double gw[5];       // gradient weights of the layers |c|^2 = 1, 2, 4, 5, 8 (Sec. 3.1.1, Table 1)
 };
 
@@ -134,9 +136,10 @@ int tile_config_ty(int i);
 // One step of every tile of `geom` (of the list `tiles_dev`, or with tiles_dev null those of the single lattice
 // doms_dev[0]), reading copy `par` and writing copy 1 - par.  `flow`, `inout`, `storage` and the gradient reach
 // `rad` (1 for E2/E4, 2 for E6/E8) must be the same for every domain referenced.  `from_hbm`: the two copies of
-// the lattices exceed the last-level cache.
+// the lattices exceed the last-level cache.  `slot`: step of a tape, whose copies lie slot * slot_stride bytes on
+// (FP32 without flow).
 hipError_t launch_step(int tile_cfg, int storage, int flow, int inout, int rad, const DomDesc* doms_dev,
-                       const TileDesc* tiles_dev, const StepGeom& geom, bool from_hbm, int par, hipStream_t s);
+                       const TileDesc* tiles_dev, const StepGeom& geom, bool from_hbm, int par, hipStream_t s, int slot = 0);
 // Grid size of a step launch over `ntiles` tiles: grid_mode 0 = one workgroup per tile,
 // 1 = persistent (one wave of resident workgroups looping over the tiles).
 int step_grid(int tile_cfg, int ntiles, int storage, int flow, int inout, int rad, int grid_mode);

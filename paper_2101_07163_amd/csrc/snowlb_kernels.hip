@@ -135,6 +135,13 @@ k_step(const DomDesc* __restrict__ doms, const TileDesc* __restrict__ tiles, int
         GMEM char* pout = (GMEM char*)d.pop[npar];
         const GMEM char* phin = (const GMEM char*)d.phip[par];
         GMEM char* phout = (GMEM char*)d.phip[npar];
+        if constexpr (!FLOW && !REF) {  // step of an adjoint tape (bits 2.. of flags)
+            const int64_t at = (int64_t)(flags >> 2) * d.slot_stride;
+            pin += at;
+            pout += at;
+            phin += at;
+            phout += at;
+        }
 
         const int x = x0 + tx, y = y0 + ty;
         const bool active = (x < nx) && (y < ny);
@@ -724,13 +731,13 @@ int step_grid(int cfg, int ntiles, int storage, int flow, int inout, int rad, in
 }
 
 hipError_t launch_step(int cfg, int storage, int flow, int inout, int rad, const DomDesc* doms_dev,
-                       const TileDesc* tiles_dev, const StepGeom& geom, bool from_hbm, int par, hipStream_t s) {
+                       const TileDesc* tiles_dev, const StepGeom& geom, bool from_hbm, int par, hipStream_t s, int slot) {
     void* fn = step_kernel(cfg, storage, flow, inout, rad, geom.grid < geom.ntiles);
     if (!fn) return hipErrorInvalidValue;
     if (geom.ntiles <= 0) return hipSuccess;
     const int nt = kTiles[cfg].tx * kTiles[cfg].ty;
     StepGeom g = geom;
-    int flags = par | (from_hbm ? 2 : 0);
+    int flags = par | (from_hbm ? 2 : 0) | slot << 2;
     void* args[] = {(void*)&doms_dev, (void*)&tiles_dev, (void*)&flags, (void*)&g.grid, (void*)&g.ntx, (void*)&g.strip,
                     (void*)&g.per, (void*)&g.m_per, (void*)&g.m_strip, (void*)&g.m_last, (void*)&g.codes, (void*)&g.ntiles};
     const int pad = storage == 0 && from_hbm ? step_lds_pad(cfg, flow, rad) : 0;
