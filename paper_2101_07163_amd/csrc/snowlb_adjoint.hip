@@ -3,7 +3,7 @@
 // For a loss L(phi_T), the adjoint lambda_t = dL/d(state at t) obeys lambda_t = (dF/ds)^T lambda_{t+1}
 // where F is one step of the phase field (Eq. (d)/(e), anisotropy of Sec. 2.1, E4 gradient of
 // Table 1) and the vapour ADR solver (Sec. 2.2.2) with u = 0.  Each reverse step is one kernel,
-// k_adj, over 64 x 16 tiles, in two passes:
+// k_adj, over 64 x 16 or 64 x 8 tiles, in two passes:
 //   pass A (per position p of the tile and of its one-cell ring): recompute the forward quantities of
 //     p from the stored state at t (phi with its halo for the gradient, a, N, eta, Q, h_eq, h*), take
 //     lambda_{t+1} of the populations p emitted (at p + c_q), and form every adjoint that is local to
@@ -32,8 +32,7 @@ __device__ constexpr float AW9[9] = {4.f / 9.f,  1.f / 9.f,  1.f / 9.f,  1.f / 9
                                      1.f / 36.f, 1.f / 36.f, 1.f / 36.f, 1.f / 36.f};
 __device__ constexpr float AW5[5] = {1.f / 3.f, 1.f / 6.f, 1.f / 6.f, 1.f / 6.f, 1.f / 6.f};
 
-constexpr int ATX = 64, ATY = 16, ANT = ATX * ATY;
-constexpr int ALX = ATX + 2, ALY = ATY + 2, ALN = ALX * ALY;
+constexpr int ATX = 64, ALX = ATX + 2;  // tiles of 64 x ATY cells, with the one-cell ring ALX wide
 
 // i mod n for any i (one add or subtract in the common case: neighbours and halos of wide lattices)
 __device__ __forceinline__ int wrapn(int i, int n) {
@@ -58,21 +57,21 @@ __device__ __forceinline__ double wave_sum_d(double v) {
 }  // namespace
 
 // LDS slots of the one-cell ring around a tile: top row, bottom row, left column, right column.
+template <int ATY>
 __device__ __forceinline__ int ring_slot(int r) {
+    constexpr int ALY = ATY + 2;
     if (r < ALX) return r;
     if (r < 2 * ALX) return (ALY - 1) * ALX + (r - ALX);
     if (r < 2 * ALX + ATY) return (1 + r - 2 * ALX) * ALX;
     return (1 + r - 2 * ALX - ATY) * ALX + ALX - 1;
 }
-// One reverse step is one kernel over 64 x 16 tiles (1024 lanes, one workgroup per CU at 512^2;
-// the one-cell ring is 16 % of the tile).  Pass B at a cell gathers B(x - c_q) and
+// One reverse step is one kernel over 64 x 16 tiles (1024 lanes, one workgroup per CU) or 64 x 8 tiles (512 lanes,
+// two per CU); the one-cell ring is 16 % or 29 % of the tile.  Pass B at a cell gathers B(x - c_q) and
 // Gbar(x - c_k) from pass A at its eight neighbours, so each workgroup runs pass A on its tile and
 // on the one-cell ring around it (the ring positions recomputed by both neighbouring workgroups
 // from the same inputs with the same code, hence bitwise equal), which needs h and phi on a two-cell
 // ring.  No intermediate plane goes through memory.
-constexpr int L2X = ATX + 4, L2Y = ATY + 4, L2N = L2X * L2Y;  // staging region: tile + two rings
-constexpr int RING1 = 2 * ALX + 2 * ATY;                     // the one-cell ring
-static_assert(RING1 <= ANT, "one ring position per lane");
+constexpr int L2X = ATX + 4;  // staging region: tile + two rings
 
 // Byte offsets of a lattice position (wrapped into the periodic lattice) and of its eight
 // neighbours, as separable x and y parts.
@@ -100,7 +99,7 @@ __device__ __forceinline__ Nb nb_of(const AdjDesc& A, int gx, int gy) {
 // c2 of the staging region), then reverse the phase-field collision and push.  Always gives B(p) and
 // Gbar(p); with FULL also reverses the vapour collision and push and gives lambda_g(p, t) (lgo),
 // lambda_phiprev(p, t) (lppo), A_h(p), the local part of phibar(p) and the eps contribution of p.
-template <bool FULL>
+template <bool FULL, int L2N>
 __device__ __forceinline__ void pass_a(const AdjDesc& A, const double* s_phi, const float (*s_h)[L2N], int c2,
                                        const float g[5], const float lh[9], const float lg[5], float lpp,
                                        float& Bv, float& Gxb, float& Gyb, float& Ah, float& phb, double& deps,
@@ -199,7 +198,11 @@ __device__ __forceinline__ void pass_a(const AdjDesc& A, const double* s_phi, co
     phb = pb_;
 }
 
-__global__ void __launch_bounds__(ANT) k_adj(AdjDesc A) {
+template <int ATY>
+__global__ void __launch_bounds__(ATX * ATY) k_adj(AdjDesc A) {
+    constexpr int ANT = ATX * ATY, ALY = ATY + 2, ALN = ALX * ALY, L2Y = ATY + 4, L2N = L2X * L2Y;
+    constexpr int RING1 = 2 * ALX + 2 * ATY;  // the one-cell ring
+    static_assert(RING1 <= ANT, "one ring position per lane");
     __shared__ double s_phi[L2N];
     __shared__ float s_h[9][L2N];
     __shared__ float s_B[ALN], s_Gx[ALN], s_Gy[ALN];
@@ -239,7 +242,7 @@ __global__ void __launch_bounds__(ANT) k_adj(AdjDesc A) {
     // ... the position of the one-cell ring this lane recomputes (pass A there needs g and
     // lambda_h(t + 1) only, loaded after the barrier) ...
     const bool has_ring = tid < RING1;
-    const int r1 = has_ring ? ring_slot(tid) : 0;  // slot in the (ALX x ALY) pass-A region
+    const int r1 = has_ring ? ring_slot<ATY>(tid) : 0;  // slot in the (ALX x ALY) pass-A region
     const Nb rn = nb_of(A, x0 + r1 % ALX - 1, y0 + r1 / ALX - 1);
     // ... and h(t) with phi(t) = sum h (FP64, as in the forward step) on the tile and two rings
     for (int r = tid; r < L2N; r += ANT) {
@@ -263,7 +266,7 @@ __global__ void __launch_bounds__(ANT) k_adj(AdjDesc A) {
     {
         const int c2 = (ty + 2) * L2X + tx + 2, c1 = (ty + 1) * ALX + tx + 1;
         float lgo[5], lppo = 0.f, Bv, Gx, Gy;
-        pass_a<true>(A, s_phi, s_h, c2, g, lh, lg, lpp, Bv, Gx, Gy, Ah, phb, deps, lgo, lppo);
+        pass_a<true, L2N>(A, s_phi, s_h, c2, g, lh, lg, lpp, Bv, Gx, Gy, Ah, phb, deps, lgo, lppo);
         s_B[c1] = Bv;
         s_Gx[c1] = Gx;
         s_Gy[c1] = Gy;
@@ -285,7 +288,7 @@ __global__ void __launch_bounds__(ANT) k_adj(AdjDesc A) {
         const int c2 = (r1 / ALX + 1) * L2X + r1 % ALX + 1;
         float Bv, Gx, Gy, ah_, ph_, lgo[5], lppo;
         double de_ = 0.0;
-        pass_a<false>(A, s_phi, s_h, c2, rg, rlh, rg, 0.f, Bv, Gx, Gy, ah_, ph_, de_, lgo, lppo);
+        pass_a<false, L2N>(A, s_phi, s_h, c2, rg, rlh, rg, 0.f, Bv, Gx, Gy, ah_, ph_, de_, lgo, lppo);
         s_B[r1] = Bv;
         s_Gx[r1] = Gx;
         s_Gy[r1] = Gy;
@@ -370,7 +373,17 @@ __global__ void __launch_bounds__(128) k_adj_final(const double* __restrict__ ep
     if (lane == 0) out[which] = t;
 }
 
-int adj_blocks(const AdjDesc& A) { return ((A.nx + ATX - 1) / ATX) * ((A.ny + ATY - 1) / ATY); }
+// Rows of a tile.  64 x 16 tiles run one per CU and have the smaller ring, so they are faster where their rounds
+// over the 256 CUs are (nearly) full: 512^2 (256 tiles) 12.0 us a step against 12.3 with 64 x 8 tiles, 1024^2 (1024)
+// 42.2 against 42.9.  Where they leave CUs idle the smaller tiles spread further: 256^2 (64 tiles) 9.1 against
+// 7.2, 141^2 8.4 against 7.1, 768^2 (576 tiles, the third round a quarter full) 28.9 against 26.0.
+static int adj_tiles(const AdjDesc& A, int rows) { return ((A.nx + ATX - 1) / ATX) * ((A.ny + rows - 1) / rows); }
+static int adj_rows(const AdjDesc& A) {
+    constexpr int kCUs = 256;
+    const int64_t t = adj_tiles(A, 16), slots = (t + kCUs - 1) / kCUs * kCUs;
+    return 8 * t >= 7 * slots ? 16 : 8;
+}
+int adj_blocks(const AdjDesc& A) { return adj_tiles(A, adj_rows(A)); }
 
 hipError_t launch_adj_seed(const AdjDesc& A, const float* dphi, hipStream_t s) {
     hipLaunchKernelGGL(k_adj_seed, dim3((A.nx + 255) / 256, A.ny), dim3(256), 0, s, A, dphi);
@@ -378,7 +391,8 @@ hipError_t launch_adj_seed(const AdjDesc& A, const float* dphi, hipStream_t s) {
 }
 
 hipError_t launch_adj_step(const AdjDesc& A, hipStream_t s) {
-    hipLaunchKernelGGL(k_adj, dim3(adj_blocks(A)), dim3(ANT), 0, s, A);
+    if (adj_rows(A) == 16) hipLaunchKernelGGL(k_adj<16>, dim3(adj_blocks(A)), dim3(ATX * 16), 0, s, A);
+    else hipLaunchKernelGGL(k_adj<8>, dim3(adj_blocks(A)), dim3(ATX * 8), 0, s, A);
     return hipGetLastError();
 }
 
