@@ -106,7 +106,8 @@ typedef struct {
     double seed_x, seed_y, seed_r; /* circular seed: centre and radius (cells)                   */
     double init_width;  /* width of the tanh seed profile (cells)                                 */
     int32_t diag_every; /* >0: snowlb_step checks for non-finite values every this many steps     */
-    int32_t tile;       /* step-kernel tile configuration; -1 = autotune, 0 = default            */
+    int32_t tile;       /* step-kernel tile configuration; -1 = autotune, 0 = default (64x4, or 128x4 or
+                           64x8 for 16-bit storage larger than the last-level cache: snowlb_get_tile) */
     int32_t stencil;    /* isotropic gradient of phi (Sec. 3.1.1): 4 = E4 (default), 6 = E6, 8 = E8
                            (Table 1 weights), 2 = E2 (the central difference of the same section);
                            E6 and E8 reach two cells and stage a two-cell halo                      */
@@ -209,7 +210,7 @@ snowlb_status snowlb_load_state(snowlb_ctx* ctx, const void* buf_dev, int64_t by
 
 /* Step-kernel tile configurations.  snowlb_tile_count() configurations exist; snowlb_tile_name(i)
  * describes one ("64x4" = 64 cells in x by 4 in y per workgroup).  snowlb_set_tile selects one for
- * a context; results are bitwise identical for every configuration.  Grid modes (0..5): bit 0 selects
+ * a context, snowlb_get_tile returns the one in use; results are bitwise identical for every configuration.  Grid modes (0..5): bit 0 selects
  * a persistent grid of resident workgroups looping over the tiles (else one workgroup per tile);
  * grid_mode >> 1 the tile order: 0 row order, 1 vertical strips 512 cells wide, 2 four vertical strips
  * of nearly equal width (each strip walked row by row).  0 is the default; the autotuner (tile = -1)

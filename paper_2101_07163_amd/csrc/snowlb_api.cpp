@@ -112,6 +112,26 @@ struct Driver {
         return SNOWLB_OK;
     }
 
+    // The default tile (after setup): 64 x 4 cells, except for 16-bit storage beyond the last-level cache.  There a
+    // line holds 64 cells of a plane, so the two halo columns of a 64 x 4 tile touch as many lines (156 with
+    // flow) as all its other loads (134).  128 x 4 tiles halve that: 2048^2 FP16 102.8 -> 95.3 us, 3000^2 224.5 ->
+    // 214.6, 1800^2 93.5 -> 84.4, without flow 2999 x 2501 109.6 -> 100.3, 64 crystals in FP16 637 -> 597.  Where odd
+    // last blocks would leave more than a twentieth of their lanes idle, 64 x 8 tiles are the faster ones (64 x 4,
+    // 128 x 4, 64 x 8: 448 x 6001 74.8, 74.8, 71.5 us; 150 x 16001 78.5, 82.5, 75.4; 18 crystals of 219^2 to 554^2
+    // 82.1, 84.1, 80.4; 832 x 3501, a thirteenth, 81.6, 77.9, 78.7).  In the cache 64 x 4 is faster (1024^2 21.3
+    // us, 22.5 with 128 x 4 and 21.6 with 64 x 8; 1523 x 1101 31.2, 32.5, 31.8), and in FP32, where a tile row is two
+    // lines (2048^2 148.0, 151.4, 152.9).
+    int default_tile() const {
+        if (storage == SNOWLB_STORE_FP32 || !from_hbm) return 0;
+        int64_t one = 0, two = 0;  // lanes of tiles one and two blocks wide
+        for (const DomDesc* d : h_doms) {
+            const int64_t rows = round_up(d->ny, kBlockY);
+            one += d->nbx * rows;
+            two += (d->nbx + 1) / 2 * 2 * rows;
+        }
+        return 20 * two <= 21 * one ? kTileTwoWide : kTileTwoHigh;
+    }
+
     void drop_graph() {
         if (graph.exec) (void)hipGraphExecDestroy(graph.exec);
         graph = StepGraph{};
@@ -776,7 +796,7 @@ snowlb_status snowlb_create(const snowlb_params* p, snowlb_ctx** out) {
         snowlb_destroy(c);
         return st;
     }
-    c->drv.tile = p->tile >= 0 ? p->tile : 0;
+    c->drv.tile = p->tile > 0 ? p->tile : c->drv.default_tile();
     if (p->tile == -1 && tune_lookup(tune_key(*p), c->drv.tile, c->drv.grid_mode)) c->tuned = true;
     *out = c;
     return SNOWLB_OK;
@@ -1353,7 +1373,7 @@ snowlb_status snowlb_batch_create(const snowlb_params* params, int32_t n, snowlb
     b->drv.rad = stencil_reach(params[0].stencil);
     snowlb_status st = b->drv.setup();
     if (st) return bail(st, b->drv.err);
-    b->drv.tile = params[0].tile >= 0 ? params[0].tile : 0;
+    b->drv.tile = params[0].tile > 0 ? params[0].tile : b->drv.default_tile();
     b->autotune = params[0].tile == -1;
     *out = b;
     return SNOWLB_OK;

@@ -129,6 +129,7 @@ struct StepGeom {
 
 // Launchers (defined in snowlb_kernels.hip).  All are asynchronous on `stream` and return the
 // hipError_t of the launch.
+constexpr int kTileTwoHigh = 1, kTileTwoWide = 3;  // the configurations of 64 x 8 and 128 x 4 cells
 int tile_config_count();
 const char* tile_config_name(int i);
 int tile_config_tx(int i);
