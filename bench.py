@@ -4,7 +4,8 @@
 Headline: coupled MLUPS (cells x steps / s / 1e6) of the ventilated 2048 x 2048 workload (D2Q9 flow
 with the crystal as a solid, D2Q5 vapour, phase field with 6-fold anisotropy; inlet u = 0.01, seed
 R = 8 at (300, 1024)) in FP32 storage, with all state resident in HBM.  One timed "step" is one
-coupled time step (the fused kernel, replayed from captured HIP graphs); exactly --steps steps are
+coupled time step (the fused kernel; 256 steps and more replay captured HIP graphs, fewer are launched
+directly); exactly --steps steps are
 timed, five times over, and the median is reported; the FP64 conservation diagnostics follow the timed
 runs and are timed on their own.  Also reported: the HBM roofline of the step kernel (algorithmic
 bytes per launch over its measured average duration), the practical copy-kernel ceiling, 16-bit
@@ -108,7 +109,7 @@ REPEATS = 5  # timed repeats of the K steps; the median is reported
 
 def time_steps(S, torch, cfg, storage, steps, warmup, tile, repeats=REPEATS, grid_mode=-1):
     """W untimed warm-up steps, then `repeats` timed runs of exactly `steps` steps, each bracketed by
-    device synchronisation, replayed from captured graphs on the current stream; the kernel time per
+    device synchronisation, on the current stream; the kernel time per
     step comes from events on that stream.  Returns the median wall time, the median event time per
     step, the timings of every repeat, and the FP64 diagnostics taken after the timed runs (their
     synchronisation is timed on its own)."""

@@ -247,7 +247,7 @@ snowlb_status snowlb_set_eps(snowlb_ctx* ctx, double eps);
 
 /* ---------------------------------------------------------------------------------------------
  * Batches: many independent crystals (each its own lattice size and parameters) advanced together,
- * one launch per step over the tiles of all domains, replayed from a captured HIP graph.  All
+ * one launch per step over the tiles of all domains (long calls replay a captured HIP graph).  All
  * domains must share flow, bc_x, storage, n_fold and the reach of the stencil (E2/E4 or E6/E8;
  * they select the kernel); everything else may differ.  Each domain evolves exactly as a context created from the same parameters would
  * (bitwise: same kernel, same per-domain arithmetic). */

@@ -147,8 +147,8 @@ struct Driver {
     // away, but the halo columns at a strip's edges lie in tiles that may run much later, on another
     // XCD.  Strips pay where each strip is a whole number of the XCDs' runs of the list, so that the
     // XCDs on the two sides of an edge walk it at the same time; which order wins depends on the
-    // lattice (2048^2 FP16 storage: 0.1058 -> 0.0988 ms with either strip order, FP32 about even;
-    // 1536^2 and 4096 x 2048: four strips 2-5 % faster; 3000^2, 6976 x 6692, 1024^2 and the
+    // lattice (2048^2 FP16 storage: 102.8 us in rows of 64 x 4 tiles, 95.1 and 98.1 in their strips, 94.5 in
+    // rows of 128 x 4 tiles, 90.7 in strips of 512 cells; FP32 about even; 1536^2 and 4096 x 2048: four strips 2-5 % faster; 3000^2, 6976 x 6692, 1024^2 and the
     // 64-crystal batch: strips 3-20 % slower), so the autotuner times every order.  The order does
     // not change any result.
     snowlb_status ensure_tiles(int cfg, int mode) {

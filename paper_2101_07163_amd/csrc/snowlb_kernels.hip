@@ -700,7 +700,7 @@ static void* step_kernel(int cfg, int storage, int flow, int inout, int rad, boo
 // XCD, 47 KB per tile with flow) evict halo and partly written lines: 2048^2 with flow reads 9 % and writes 4 %
 // more than with the limit and takes 159 us instead of 148 to 149 (3000^2 359 and 323; 12 waves 321, but the
 // 64-crystal batch 960 instead of 900); without flow 2048^2 96.9, 92.9 with 16, 112.7 with 12.  16-bit storage
-// (29 KB per tile) keeps them all (2048^2 FP16 99.1 us, 96.9 to 100.5 with 16 to 20 waves, 126.8 with 12; 1024^2
+// keeps them all (2048^2 FP16 with 128 x 4 tiles 94.5 us, 97.9 with 16 waves, 100.0 with 8; 1024^2 with 64 x 4 tiles
 // 21.7, 23.7 with 16).
 static int step_lds_pad(int cfg, int flow, int rad) {
     const TileCfg& t = kTiles[cfg];
