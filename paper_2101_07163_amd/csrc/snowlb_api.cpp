@@ -20,6 +20,7 @@
 
 #include "../../include/snowlb.h"
 #include "snowlb_internal.h"
+#include "snowlb_io.h"
 
 using namespace snowlb;
 
@@ -709,6 +710,7 @@ int64_t ctx_state_bytes(const snowlb_ctx* c) { return kHeaderBytes + c->pop_byte
 struct snowlb_batch {
     std::vector<snowlb_ctx*> doms;
     DomDesc* d_doms = nullptr;
+    InitArgs* d_init = nullptr;  // initial state of every domain
     Driver drv;
     int64_t cells = 0;
     bool inited = false;
@@ -1325,6 +1327,7 @@ void snowlb_batch_destroy(snowlb_batch* b) {
     (void)hipDeviceSynchronize();
     b->drv.release();
     if (b->d_doms) (void)hipFree(b->d_doms);
+    if (b->d_init) (void)hipFree(b->d_init);
     for (snowlb_ctx* c : b->doms) snowlb_destroy(c);
     delete b;
 }
@@ -1375,6 +1378,19 @@ snowlb_status snowlb_batch_create(const snowlb_params* params, int32_t n, snowlb
     if (st) return bail(st, b->drv.err);
     b->drv.tile = params[0].tile > 0 ? params[0].tile : b->drv.default_tile();
     b->autotune = params[0].tile == -1;
+    if (n > 1) {
+        std::vector<InitArgs> init;
+        for (int i = 0; i < n; ++i) {
+            const snowlb_params& p = params[i];
+            init.push_back({nullptr, (float)p.U0, (float)p.seed_x, (float)p.seed_y, (float)p.seed_r, (float)p.init_width,
+                            (float)p.u_in});
+        }
+        e = hipMalloc(&b->d_init, init.size() * sizeof(InitArgs));
+        if (e != hipSuccess) return bail(hip_status(e), hip_msg(e, "hipMalloc(initial states)"));
+        e = hipMemcpy(b->d_init, init.data(), init.size() * sizeof(InitArgs), hipMemcpyHostToDevice);
+        if (e != hipSuccess) return bail(hip_status(e), hip_msg(e, "hipMemcpy(initial states)"));
+        if ((st = b->drv.ensure_tiles(0, 0))) return bail(st, b->drv.err);
+    }
     *out = b;
     return SNOWLB_OK;
 }
@@ -1385,12 +1401,25 @@ int64_t snowlb_batch_step_count(const snowlb_batch* b) { return b ? b->drv.step 
 
 snowlb_status snowlb_batch_init(snowlb_batch* b, void* stream) {
     if (!b) return SNOWLB_EINVAL;
-    for (snowlb_ctx* c : b->doms) {
-        snowlb_status st = ctx_init(c, nullptr, (hipStream_t)stream);
-        if (st) {
-            b->err = c->err;
-            return st;
+    if (b->d_init) {
+        const int li = Driver::list_index(0, 0);
+        const hipError_t e = launch_init_batch(b->drv.storage, b->d_doms, b->drv.d_tiles[li], b->drv.geoms[li].ntiles,
+                                               b->d_init, (hipStream_t)stream);
+        if (e != hipSuccess) {
+            b->err = hip_msg(e, "init kernel");
+            return hip_status(e);
         }
+    }
+    for (snowlb_ctx* c : b->doms) {
+        if (!b->d_init) {
+            if (snowlb_status st = ctx_init(c, nullptr, (hipStream_t)stream)) {
+                b->err = c->err;
+                return st;
+            }
+        }
+        c->drv.par = 0;
+        c->drv.step = 0;
+        c->inited = true;
     }
     b->drv.par = 0;
     b->drv.step = 0;
