@@ -29,36 +29,41 @@ __device__ __forceinline__ GMEM float* phip_ptr(const DomDesc& d, int par) {
 }
 
 // Reference values (U, rho, jx, jy) of lattice position (gx, gy) with the closure: the inlet ghost
-// carries (U_in, rho0, rho0 u_in, 0) rounded to the storage format.
+// carries (U_in, rho0, rho0 u_in, 0) rounded to the storage format.  Loaded first, converted where they are used, so
+// that loads of several positions are in flight together.
+template <class S>
+struct StoredRef {
+    typename S::T v[4];
+    bool inlet;
+};
+template <class S>
+__device__ __forceinline__ StoredRef<S> load_ref(const DomDesc& d, int par, int gx, int gy) {
+    StoredRef<S> r{};
+    r.inlet = d.inout && gx < 0;
+    gx = d.inout ? min(max(gx, 0), d.nx - 1) : wrapi(gx, d.nx);
+    const int64_t i = cell_index(d.nbx, d.nqb, gx, wrapi(gy, d.ny));
+    const GMEM typename S::T* b = (const GMEM typename S::T*)(d.refs[par]);
+    r.v[R_U] = b[i];
+    if (d.npop == 23) {
+        r.v[R_RHO] = b[d.rplane + i];
+        r.v[R_JX] = b[2 * d.rplane + i];
+        r.v[R_JY] = b[3 * d.rplane + i];
+    }
+    return r;
+}
+template <class S>
+__device__ __forceinline__ void ref_value(const DomDesc& d, const StoredRef<S>& t, float r[4]) {
+    const bool flow = d.npop == 23;
+    r[R_U] = S::from_ref(t.inlet ? S::to_ref(d.U_in) : t.v[R_U]);
+    r[R_RHO] = flow ? S::from_ref(t.inlet ? S::to_ref(d.ref_f) : t.v[R_RHO]) : 0.f;
+    r[R_JX] = flow ? S::from_ref(t.inlet ? S::to_ref(d.ref_f * d.u_in) : t.v[R_JX]) : 0.f;
+    r[R_JY] = flow && !t.inlet ? S::from_ref(t.v[R_JY]) : 0.f;
+}
+
 template <class S>
 __device__ __forceinline__ void ref_at(const DomDesc& d, int par, int gx, int gy, float r[4]) {
-    if (!S::kLocalRef) {
-        r[0] = r[1] = r[2] = r[3] = 0.f;
-        return;
-    }
-    const int sy = wrapi(gy, d.ny);
-    if (d.inout) {
-        if (gx < 0) {
-            r[R_U] = S::from_ref(S::to_ref(d.U_in));
-            r[R_RHO] = S::from_ref(S::to_ref(d.ref_f));
-            r[R_JX] = S::from_ref(S::to_ref(d.ref_f * d.u_in));
-            r[R_JY] = 0.f;
-            return;
-        }
-        if (gx >= d.nx) gx = d.nx - 1;
-    } else {
-        gx = wrapi(gx, d.nx);
-    }
-    const int64_t i = cell_index(d.nbx, d.nqb, gx, sy);
-    const GMEM typename S::T* b = (const GMEM typename S::T*)(d.refs[par]);
-    r[R_U] = S::from_ref(b[i]);
-    if (d.npop == 23) {
-        r[R_RHO] = S::from_ref(b[d.rplane + i]);
-        r[R_JX] = S::from_ref(b[2 * d.rplane + i]);
-        r[R_JY] = S::from_ref(b[3 * d.rplane + i]);
-    } else {
-        r[R_RHO] = r[R_JX] = r[R_JY] = 0.f;
-    }
+    if constexpr (S::kLocalRef) ref_value<S>(d, load_ref<S>(d, par, gx, gy), r);
+    else r[0] = r[1] = r[2] = r[3] = 0.f;
 }
 
 // Cell of a lane: a workgroup of 256 lanes takes one 64 x 4 block, whose planes are contiguous in memory, so every
@@ -108,25 +113,37 @@ __device__ __forceinline__ void decode_f(const typename S::T raw[9], const R& re
 
 // The references of a block and its one-cell ring in LDS (16-bit storage): each is formed once per position
 // instead of once per population that needs it (2048^2 FP16 from the nine sources of each cell: initial
-// state 85 us, read of rho 69 us, of U 44 us).  at(gx, gy, r) gives those of a lattice position; every lane of
-// the workgroup calls the constructor.
+// state 85 us, now 60, read of rho 69 us, of U 44 us; with the ring's loads waiting for the block's 40 and 34 us, together 29
+// and 25).  load(gx, gy) gives those of a lattice position in a form that value() turns into floats; every lane of the
+// workgroup calls the constructor.
 template <class S>
 struct BlockRefs {
     static constexpr int LX = kBlockX + 2, LY = kBlockY + 2, N = S::kLocalRef ? LX * LY : 1;
     const float (*s)[N];
     int own;
-    template <class A>
-    __device__ __forceinline__ BlockRefs(float (*lds)[N], int x0, int y0, const A& at) : s(lds) {
-        const int tid = threadIdx.x;
-        own = (tid / kBlockX + 1) * LX + tid % kBlockX + 1;
-        if (!S::kLocalRef) return;
-        for (int p = tid; p < N; p += kBlockCells) {
+    // Every lane takes its own cell and the first lanes one position of the ring each.
+    template <class L, class V>
+    __device__ __forceinline__ BlockRefs(float (*lds)[N], int x0, int y0, const L& load, const V& value) : s(lds) {
+        const int tid = threadIdx.x, tx = tid % kBlockX + 1, ty = tid / kBlockX + 1;
+        own = ty * LX + tx;
+        if constexpr (S::kLocalRef) {
+            constexpr int RING = N - kBlockCells;
+            const int c = tid - 2 * LX;
+            const int rx = tid < 2 * LX ? tid % LX : (c & 1) * (LX - 1), ry = tid < 2 * LX ? tid / LX * (LY - 1) : 1 + c / 2;
+            const auto a = load(x0 + tx - 1, y0 + ty - 1);
+            auto b = a;
+            if (tid < RING) b = load(x0 + rx - 1, y0 + ry - 1);
             float r[4];
-            at(x0 + p % LX - 1, y0 + p / LX - 1, r);
+            value(a, r);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) lds[k][p] = r[k];
+            for (int k = 0; k < 4; ++k) lds[k][own] = r[k];
+            if (tid < RING) {
+                value(b, r);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) lds[k][ry * LX + rx] = r[k];
+            }
+            __syncthreads();
         }
-        __syncthreads();
     }
     __device__ __forceinline__ void operator()(int dx, int dy, float r[4]) const {
 #pragma unroll
@@ -137,7 +154,8 @@ template <class S>
 __device__ __forceinline__ BlockRefs<S> block_refs(const DomDesc& d, int par) {
     __shared__ float lds[4][BlockRefs<S>::N];
     return BlockRefs<S>(lds, blockIdx.x * kBlockX, blockIdx.y * kBlockY,
-                        [&](int gx, int gy, float r[4]) { ref_at<S>(d, par, gx, gy, r); });
+                        [&](int gx, int gy) { return load_ref<S>(d, par, gx, gy); },
+                        [&](const StoredRef<S>& t, float r[4]) { ref_value<S>(d, t, r); });
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -152,7 +170,7 @@ __device__ __forceinline__ void init_at(const DomDesc& d, const InitArgs& a, int
     U = a.U_init ? a.U_init[(int64_t)y * d.nx + x] : a.U0;
 }
 
-// Reference values of the initial state at any lattice position, with the closure of ref_at.
+// Reference values of the initial state at any lattice position, with the closure of load_ref.
 template <class S>
 __device__ __forceinline__ void init_ref_at(const DomDesc& d, const InitArgs& a, int gx, int gy, float r[4]) {
     const int sy = wrapi(gy, d.ny);
@@ -181,7 +199,9 @@ template <class S>
 __device__ __forceinline__ void init_block(const DomDesc& d, int par, const InitArgs& a, int x0, int y0) {
     const int x = x0 + threadIdx.x % kBlockX, y = y0 + threadIdx.x / kBlockX;
     __shared__ float lds[4][BlockRefs<S>::N];
-    const BlockRefs<S> refs(lds, x0, y0, [&](int gx, int gy, float r[4]) { init_ref_at<S>(d, a, gx, gy, r); });
+    const BlockRefs<S> refs(
+        lds, x0, y0, [](int gx, int gy) { return int2{gx, gy}; },
+        [&](int2 at, float r[4]) { init_ref_at<S>(d, a, at.x, at.y, r); });
     if (x >= d.nx || y >= d.ny) return;
     const bool flow = d.npop == 23;
     const float rho0 = d.ref_f;
