@@ -182,17 +182,21 @@ k_step(const DomDesc* __restrict__ doms, const TileDesc* __restrict__ tiles, int
 
         // ---- issue every global load of this tile first: the cell's own h, phi_prev (and 16-bit references), g
         // and f, which are one contiguous run per workgroup, then the halo ring.  The loads are
-        // unconditional (a lane outside the domain, or on the inlet ghost, loads the position the closure
-        // maps it to), so that they form one block and nothing is computed before the last is issued.  The
+        // unconditional, so that they form one block and nothing is computed before the last is issued.  The
         // ring before f and g lets the staging start earlier (1024^2 FP32 30.6 instead of 30.8 us) but
         // splits the run, which costs HBM-sized lattices 1.8 % (2048^2 149.5 against 146.7 us); h before g and
-        // f, kept apart from them, is worth 2 % on small lattices (256^2 4.7 -> 4.6 us).  Lanes
-        // outside the domain stage the position their LDS slot stands for, which can be the halo of an
-        // active neighbour.
+        // f, kept apart from them, is worth 2 % on small lattices (256^2 4.7 -> 4.6 us).
+        // A lane up to RAD cells outside the domain stages the h of the position its LDS slot stands for, the halo of an
+        // active neighbour.  What an idle lane stages further out and its g and f are read by nobody: they
+        // come from the last column and row, whose lines the active lanes load anyway (from the position the
+        // closure maps the lane to they were lines of the far side: 16001 x 5 with flow 8.4 -> 6.7 us, 65 x 20001
+        // 79.8 -> 73.2, habit batch of 400^2 22.0 -> 21.8; a branch around them costs full tiles 2 to 4 %).
         T graw[5], fraw[9], hraw[9], rraw[SLOTS][9];
         T oref[NR], rref[SLOTS][NR];
         float rphi[SLOTS];  // phi_prev of the staged ring positions
-        const int osx = cx(x), osy = cy(y);  // (x, y) itself for active lanes
+        const int px = x - nx, py = y - ny;
+        const int osx = px < 0 ? x : (!INOUT && px < RAD ? px : nx - 1), osy = py < 0 ? y : (py < RAD ? py : ny - 1);
+        const uint32_t xg = xof(min(x, nx - 1));
         const uint32_t xo = xof(osx), yo = yof(osy), xo1 = xof1(osx), yo1 = yof1(osy);
         const Row own_row = row_of(ROWS, yo, 0, NP - 1);
 #pragma unroll
@@ -204,11 +208,11 @@ k_step(const DomDesc* __restrict__ doms, const TileDesc* __restrict__ tiles, int
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int q = 0; q < 5; ++q) graw[q] = own_row.get(PG + q, xo);
+        for (int q = 0; q < 5; ++q) graw[q] = own_row.get(PG + q, xg);
         __builtin_amdgcn_sched_barrier(0);
         if (FLOW) {
 #pragma unroll
-            for (int q = 0; q < 9; ++q) fraw[q] = own_row.get(PF + q, xo);
+            for (int q = 0; q < 9; ++q) fraw[q] = own_row.get(PF + q, xg);
         }
         // Ring position r in the staged region.  One cell wide: the rows below and above the tile, corners included,
         // then the columns.  Two cells wide: the four rows of TX cells, aligned like the tile's own (a wave's
