@@ -553,9 +553,12 @@ hipError_t launch_pop_io(const DomDesc& d, int par, int set, int to_canon, float
 // across waves, one partial per workgroup, then a single-workgroup pass in a fixed order.
 static constexpr int kDiagThreads = 256;
 
+// Four cells a lane in FP32, one in 16 bits, where a cell is a long chain (its references, then its populations): fewer
+// partials cost k_diag_final less, more lanes hide the chain (both kernels, 1024^2 FP32 23.1 us with four, 25.0 with one;
+// 701 x 499 without flow 10.4 and 13.8; 128^2 FP16 15.6 and 9.3, 701 x 499 19.7 and 17.6).
 int diag_blocks(const DomDesc& d) {
-    const long cells = (long)d.nx * d.ny;
-    long b = (cells + kDiagThreads - 1) / kDiagThreads;
+    const long cells = (long)d.nx * d.ny, per = kDiagThreads * (d.storage == 0 ? 4 : 1);
+    long b = (cells + per - 1) / per;
     if (b > kDiagMaxBlocks) b = kDiagMaxBlocks;  // larger lattices loop over more cells per thread
     return (int)(b < 1 ? 1 : b);
 }
@@ -657,12 +660,21 @@ __global__ void __launch_bounds__(256) k_diag_final(const double* __restrict__ p
     // 32 lanes per quantity: lane l of quantity k sums blocks l, l + 32, ... in order, then lane 0
     // adds the 32 lane sums in order.  Fixed order, hence deterministic.  Then the species invariant
     // sum U + (L_sat/2) sum phi_prev (the vapour the depletion source of Sec. 2.2.2 removes is
-    // (L_sat/2) times the phase gained).
+    // (L_sat/2) times the phase gained).  A lane loads a batch of its partials before it adds the first: the
+    // kernel is bound by the latency of those loads (one by one, 2048 blocks took 17 to 20 us: diagnostics of 1024^2
+    // FP16 41 us, now 28; 2048^2 FP32 95, now 81).
+    constexpr int kBatch = 16;
     __shared__ double s[8][32];
     __shared__ double tot[8];
-    const int k = threadIdx.x / 32, l = threadIdx.x % 32;
+    const int k = threadIdx.x % 8, l = threadIdx.x / 8;
     double v = 0;
-    for (int b = l; b < nblk; b += 32) v += partials[(int64_t)b * 8 + k];
+    for (int b = l; b < nblk; b += 32 * kBatch) {
+        double p[kBatch];
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) p[i] = b + 32 * i < nblk ? partials[(int64_t)(b + 32 * i) * 8 + k] : 0.0;
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) v += p[i];
+    }
     s[k][l] = v;
     __syncthreads();
     if (l == 0) {
