@@ -76,6 +76,25 @@ __device__ __forceinline__ void lane_cell(int& x, int& y) {
 }
 static dim3 block_grid(const DomDesc& d) { return dim3(d.nbx, (d.ny + kBlockY - 1) / kBlockY); }
 
+// The same with each XCD taking a contiguous run of blocks, for canonical rows of another length than whole lines: a block
+// then reads three lines a row, and the blocks that share the outer two lie on one L2.  (On eight XCDs they
+// fetch them twice: h of 1500 x 1100 FP32 22.9 us, in runs 18.6, in rows of 256 x 1 cells 20.6; 2049 x 2047 FP16 47.9, 36.5,
+// 40.2; 3000 x 1500 FP32 57.8, 60.8, 58.0.  With whole lines runs only cost their division: 1024^2 FP16 10.0 and
+// 10.4.)
+__device__ __forceinline__ void lane_cell_runs(int& x, int& y) {
+    const uint32_t G = gridDim.x * gridDim.y, b = blockIdx.y * gridDim.x + blockIdx.x;
+    const uint32_t xcd = b % 8, slot = xcd * (G / 8) + min(xcd, G % 8) + b / 8, by = slot / gridDim.x;
+    x = (int)(slot - by * gridDim.x) * kBlockX + threadIdx.x % kBlockX;
+    y = (int)by * kBlockY + threadIdx.x / kBlockX;
+}
+
+// Rows of 256 x 1 cells per workgroup.
+__device__ __forceinline__ void lane_cell_rows(int& x, int& y) {
+    x = blockIdx.x * kBlockCells + threadIdx.x;
+    y = blockIdx.y;
+}
+static dim3 row_grid(const DomDesc& d) { return dim3((d.nx + kBlockCells - 1) / kBlockCells, d.ny); }
+
 // Decode one population set of an in-domain cell; sets that are not asked for are not loaded.
 template <class S>
 __device__ __forceinline__ void decode_h(const DomDesc& d, int par, int x, int y, float h[9]) {
@@ -194,10 +213,9 @@ __device__ __forceinline__ void init_ref_at(const DomDesc& d, const InitArgs& a,
     r[R_JY] = 0.f;
 }
 
-// The block of 64 x 4 cells at (x0, y0).
+// Cell (x, y) of the lane; with 16-bit storage the workgroup has the block of 64 x 4 cells at (x0, y0).
 template <class S>
-__device__ __forceinline__ void init_block(const DomDesc& d, int par, const InitArgs& a, int x0, int y0) {
-    const int x = x0 + threadIdx.x % kBlockX, y = y0 + threadIdx.x / kBlockX;
+__device__ __forceinline__ void init_cell(const DomDesc& d, int par, const InitArgs& a, int x, int y, int x0, int y0) {
     __shared__ float lds[4][BlockRefs<S>::N];
     const BlockRefs<S> refs(
         lds, x0, y0, [](int gx, int gy) { return int2{gx, gy}; },
@@ -246,9 +264,13 @@ __device__ __forceinline__ void init_block(const DomDesc& d, int par, const Init
     }
 }
 
-template <class S>
+template <class S, bool ROWS>
 __global__ void __launch_bounds__(kBlockCells) k_init(DomDesc d, int par, InitArgs a) {
-    init_block<S>(d, par, a, blockIdx.x * kBlockX, blockIdx.y * kBlockY);
+    static_assert(!(ROWS && S::kLocalRef), "16-bit references are formed by block");
+    int x, y;
+    if (ROWS) lane_cell_rows(x, y);
+    else lane_cell(x, y);
+    init_cell<S>(d, par, a, x, y, blockIdx.x * kBlockX, blockIdx.y * kBlockY);
 }
 
 // Every lattice of a batch in one launch over its list of 64 x 4 tiles: a launch per lattice leaves most of the chip
@@ -259,7 +281,7 @@ __global__ void __launch_bounds__(kBlockCells)
     k_init_batch(const DomDesc* __restrict__ doms, const TileDesc* __restrict__ tiles, const InitArgs* __restrict__ args) {
     const TileDesc t = tiles[blockIdx.x];
     const DomDesc d = doms[t.dom];
-    init_block<S>(d, 0, args[t.dom], t.x0, t.y0);
+    init_cell<S>(d, 0, args[t.dom], t.x0 + threadIdx.x % kBlockX, t.y0 + threadIdx.x / kBlockX, t.x0, t.y0);
 }
 
 hipError_t launch_init_batch(int storage, const DomDesc* doms, const TileDesc* tiles, int ntiles, const InitArgs* args,
@@ -276,7 +298,16 @@ hipError_t launch_init_batch(int storage, const DomDesc* doms, const TileDesc* t
 
 template <class S>
 static hipError_t init_s(const DomDesc& d, int par, const InitArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL(k_init<S>, block_grid(d), dim3(kBlockCells), 0, s, d, par, a);
+    // Blocks, except where they would leave a quarter of their lanes idle: there rows do better in FP32 (2048^2 with flow
+    // 71.8 us in blocks, 79.1 in rows, 3000 x 1500 without flow 52.7 and 58.9; 65 x 20001 29.4 and 27.0).
+    if constexpr (!S::kLocalRef) {
+        const int64_t lanes = (int64_t)d.nbx * kBlockX * ((d.ny + kBlockY - 1) / kBlockY * kBlockY);
+        if (4 * (int64_t)d.nx * d.ny <= 3 * lanes) {
+            hipLaunchKernelGGL((k_init<S, true>), row_grid(d), dim3(kBlockCells), 0, s, d, par, a);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((k_init<S, false>), block_grid(d), dim3(kBlockCells), 0, s, d, par, a);
     return hipGetLastError();
 }
 
@@ -372,11 +403,14 @@ hipError_t launch_read(const DomDesc& d, int par, int field, float* dst, hipStre
 // collisions currently see (0 without flow).  16-bit storage encodes h against the new phi_prev and g
 // against a U reference reset to 0 (inlet-ghost sources keep the ghost constant), as a population
 // write does.  The U case reads only f, h and phi_prev, none of which it writes.
+// Rows in FP32, blocks in 16 bits: phi of 65 x 20001 FP32 13.7 and 14.7 us, FP16 13.0 and 11.0; U with flow 27.4 and 30.6,
+// FP16 33.3 and 30.4.
 template <class S>
 __global__ void __launch_bounds__(kBlockCells) k_write_field(DomDesc d, int par, int field,
                                                              const float* __restrict__ src) {
     int x, y;
-    lane_cell(x, y);
+    if (S::kLocalRef) lane_cell(x, y);
+    else lane_cell_rows(x, y);
     if (x >= d.nx || y >= d.ny) return;
     const int64_t i = cell_index(d.nbx, d.nqb, x, y), i1 = cell_index(d.nbx, 1, x, y);
     const float v = src[(int64_t)y * d.nx + x];
@@ -424,7 +458,7 @@ __global__ void __launch_bounds__(kBlockCells) k_write_field(DomDesc d, int par,
 
 template <class S>
 static hipError_t write_field_s(const DomDesc& d, int par, int field, const float* src, hipStream_t s) {
-    hipLaunchKernelGGL(k_write_field<S>, block_grid(d), dim3(kBlockCells), 0, s, d, par, field, src);
+    hipLaunchKernelGGL(k_write_field<S>, S::kLocalRef ? block_grid(d) : row_grid(d), dim3(kBlockCells), 0, s, d, par, field, src);
     return hipGetLastError();
 }
 
@@ -478,7 +512,8 @@ __device__ __forceinline__ typename S::T enc_deviation(float p, float iw, float 
 template <class S, int SET>
 __global__ void __launch_bounds__(kBlockCells) k_pop_set(DomDesc d, int par, const float* __restrict__ canon) {
     int x, y;
-    lane_cell(x, y);
+    if (SET != 3 && d.nx % 32) lane_cell_runs(x, y);
+    else lane_cell(x, y);
     if (x >= d.nx || y >= d.ny) return;
     const int64_t n = (int64_t)d.nx * d.ny, c = (int64_t)y * d.nx + x, i = cell_index(d.nbx, d.nqb, x, y);
     const int64_t i1 = cell_index(d.nbx, 1, x, y), ir = i;
