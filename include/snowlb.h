@@ -28,8 +28,9 @@
  *   SNOWLB_TUNE_STEPS      steps per timing sample of the autotuner (default 20, even)
  *   SNOWLB_BUFFER_STAGGER  bytes added after each 64 KiB-padded buffer of a lattice so that the
  *                          buffers a tile touches start on different HBM channels (default 2304)
- *   SNOWLB_GRAPH_STEPS     steps per captured graph of snowlb_step (default 32, even); calls of fewer
- *                          than eight graphs' steps, and the rest of longer ones, are launched directly
+ *   SNOWLB_GRAPH_STEPS     steps per captured graph of snowlb_step (default 32, even); calls of which
+ *                          whole graphs cover less than four fifths, calls of fewer than eight graphs on
+ *                          more than 2^17 cells, and the rest of others are launched directly
  *   SNOWLB_NO_GRAPH        1: launch every step directly instead of replaying graphs
  *   SNOWLB_ADJ_OVERLAP     0: run the adjoint backward pass in serial order on the caller's stream
  *                          (default 1: recompute the next checkpoint interval on a second stream of
@@ -247,7 +248,7 @@ snowlb_status snowlb_set_eps(snowlb_ctx* ctx, double eps);
 
 /* ---------------------------------------------------------------------------------------------
  * Batches: many independent crystals (each its own lattice size and parameters) advanced together,
- * one launch per step over the tiles of all domains (long calls replay a captured HIP graph).  All
+ * one launch per step over the tiles of all domains, replayed from a captured HIP graph as in snowlb_step.  All
  * domains must share flow, bc_x, storage, n_fold and the reach of the stencil (E2/E4 or E6/E8;
  * they select the kernel); everything else may differ.  Each domain evolves exactly as a context created from the same parameters would
  * (bitwise: same kernel, same per-domain arithmetic). */

@@ -71,7 +71,7 @@ const char* snowlb3d_last_error(const snowlb3d_ctx* ctx);
  * h_q = w_q phi0, phi_prev = phi0, equilibrium f and g at the velocity (1 - phi0)/2 (u_in, 0, 0) when
  * ventilated (0 otherwise).  Resets the step count. */
 snowlb_status snowlb3d_init(snowlb3d_ctx* ctx, const float* U_init_dev, void* stream);
-/* Advance n >= 0 steps (asynchronous; long calls replay a captured graph).  ESTATE before init. */
+/* Advance n >= 0 steps (asynchronous; replayed from a captured graph as in snowlb_step).  ESTATE before init. */
 snowlb_status snowlb3d_step(snowlb3d_ctx* ctx, int32_t n, void* stream);
 int64_t snowlb3d_step_count(const snowlb3d_ctx* ctx);
 /* A macroscopic field (SNOWLB3D_FIELD_*) into dst_dev (dst_elems >= nx*ny*nz floats). */

@@ -13,6 +13,7 @@
 
 #include "../../include/snowlb3d.h"
 #include "snowlb3d_internal.h"
+#include "snowlb_graph.h"
 
 using namespace snowlb3d;
 
@@ -205,14 +206,12 @@ snowlb_status plain3(snowlb3d_ctx* c, int n, hipStream_t s) {
     return SNOWLB_OK;
 }
 
-// n steps: direct launches (at 2.8 us of host time each they keep ahead of any 3D step, and nothing has to be
-// captured); calls of many graphs' steps replay graphs of K steps, which leave the host free, after one
-// direct launch if the state sits in copy 1.
+// n steps, by graphs of K steps and direct launches as in two dimensions.
 snowlb_status run3(snowlb3d_ctx* c, int n, hipStream_t s) {
-    constexpr int kGraphRuns = 8;
     const int K = std::max(2, env_int("SNOWLB_GRAPH_STEPS", 32) & ~1);
     snowlb_status st = SNOWLB_OK;
-    if (n / K >= kGraphRuns && !env_int("SNOWLB_NO_GRAPH", 0)) {
+    const int64_t cells = (int64_t)c->p.nx * c->p.ny * c->p.nz;
+    if (snowlb::replays_graphs(n, K, c->par, cells) && !env_int("SNOWLB_NO_GRAPH", 0) && !snowlb::being_captured(s)) {
         if (c->par == 1) {
             if ((st = plain3(c, 1, s))) return st;
             n -= 1;

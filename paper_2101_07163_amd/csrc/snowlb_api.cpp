@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "../../include/snowlb.h"
+#include "snowlb_graph.h"
 #include "snowlb_internal.h"
 #include "snowlb_io.h"
 
@@ -65,6 +66,7 @@ struct Driver {
     std::vector<const DomDesc*> h_doms;  // host copies (geometry for the tile lists)
     int storage = 0, flow = 0, inout = 0, rad = 1;
     bool from_hbm = false;  // the two copies of all lattices exceed the last-level cache
+    int64_t cells = 0;      // of all lattices
     // grid_mode (launch mode): bit 0 = persistent grid (else one workgroup per tile), grid_mode >> 1 =
     // tile order; see ensure_tiles
     int tile = 0, grid_mode = 0;
@@ -103,8 +105,10 @@ struct Driver {
 
     snowlb_status setup() {
         int64_t bytes = 0;
-        for (const DomDesc* d : h_doms)
+        for (const DomDesc* d : h_doms) {
+            cells += (int64_t)d->nx * d->ny;
             bytes += 2 * (int64_t)d->nbx * kBlockX * round_up(d->ny, kBlockY) * (d->nqb * (d->storage == SNOWLB_STORE_FP32 ? 4 : 2) + 4);
+        }
         from_hbm = bytes > kLastLevelCache;
         d_tiles.assign(kTileOrders * tile_config_count(), nullptr);
         geoms.assign(kTileOrders * tile_config_count(), StepGeom{});
@@ -241,18 +245,14 @@ struct Driver {
         return SNOWLB_OK;
     }
 
-    // n steps with the current configuration.  Calls of fewer than kGraphRuns graphs' steps are launched directly:
-    // a direct launch costs the host 2.8 us, less than the smallest step, and steps follow each other a
-    // little faster than inside a graph (128^2 3.4 us against 3.5, 512^2 6.2 against 6.4), while a graph has to
-    // be captured first and short graphs for a remainder leave gaps between them (50 steps of 128^2: 237 us
-    // as one graph of 32 and nine of two).  Long calls replay graphs of K steps, which leave the host free
-    // (1.1 us a step), after one direct launch if the state sits in copy 1 (the graph starts from copy 0).
-    static constexpr int kGraphRuns = 8;
+    // n steps with the current configuration: whole graphs of K steps where replays_graphs says so, after one direct
+    // launch if the state sits in copy 1; direct launches for the rest, and for other calls (50 steps of 128^2 as one
+    // graph of 32 and nine of two: 237 us, directly 170).
     snowlb_status run(int n, hipStream_t s) {
         snowlb_status st = ensure_tiles(tile, grid_mode);
         if (st) return st;
         const int K = std::max(2, env_int("SNOWLB_GRAPH_STEPS", 32) & ~1);
-        if (n / K >= kGraphRuns && !env_int("SNOWLB_NO_GRAPH", 0)) {
+        if (replays_graphs(n, K, par, cells) && !env_int("SNOWLB_NO_GRAPH", 0) && !being_captured(s)) {
             if (par == 1) {
                 if ((st = plain(tile, grid_mode, 1, s))) return st;
                 n -= 1;
