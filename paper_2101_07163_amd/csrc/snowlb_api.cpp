@@ -74,6 +74,7 @@ struct Driver {
     // for batches, the list of tiles
     std::vector<TileDesc*> d_tiles;
     std::vector<StepGeom> geoms;
+    std::vector<int> persistent;  // workgroups of a persistent grid, same index (0: not asked for yet)
     int par = 0;
     int64_t step = 0;
     hipStream_t cap_stream = nullptr;
@@ -112,6 +113,7 @@ struct Driver {
         from_hbm = bytes > kLastLevelCache;
         d_tiles.assign(kTileOrders * tile_config_count(), nullptr);
         geoms.assign(kTileOrders * tile_config_count(), StepGeom{});
+        persistent.assign(kTileOrders * tile_config_count(), 0);
         hipError_t e = hipStreamCreateWithFlags(&cap_stream, hipStreamNonBlocking);
         if (e != hipSuccess) return hipfail(e, "hipStreamCreate");
         return SNOWLB_OK;
@@ -144,6 +146,17 @@ struct Driver {
 
     static int list_index(int cfg, int mode) { return kTileOrders * cfg + (mode >> 1); }
 
+    // What a launch of (cfg, mode) needs, made once: its tiles, and the size of a persistent grid (asking for it on every call
+    // costs short calls 1 to 2 us each).
+    snowlb_status ensure_tiles(int cfg, int mode) {
+        const int li = list_index(cfg, mode);
+        if (!geoms[li].ntiles)
+            if (snowlb_status st = build_tiles(cfg, mode)) return st;
+        if ((mode & 1) && !persistent[li])
+            persistent[li] = step_grid(cfg, geoms[li].ntiles, storage, flow, inout, rad);
+        return SNOWLB_OK;
+    }
+
     // Tiles of configuration cfg in the order of launch mode `mode`: a list for a batch, the geometry alone for a
     // single lattice (its kernel computes them, which saves a dependent load per workgroup).  Row order walks each lattice
     // row of tiles by row of tiles.  The strip orders cut each lattice into vertical strips, 512 cells
@@ -156,10 +169,9 @@ struct Driver {
     // rows of 128 x 4 tiles, 90.7 in strips of 512 cells; FP32 about even; 1536^2 and 4096 x 2048: four strips 2-5 % faster; 3000^2, 6976 x 6692, 1024^2 and the
     // 64-crystal batch: strips 3-20 % slower), so the autotuner times every order.  The order does
     // not change any result.
-    snowlb_status ensure_tiles(int cfg, int mode) {
+    snowlb_status build_tiles(int cfg, int mode) {
         const int li = list_index(cfg, mode);
         StepGeom& geo = geoms[li];
-        if (geo.ntiles) return SNOWLB_OK;
         const int TX = tile_config_tx(cfg), TY = tile_config_ty(cfg);
         std::vector<TileDesc> t;
         constexpr int kStripCells = 512;
@@ -193,8 +205,10 @@ struct Driver {
 
     // launch geometry of (cfg, mode), after ensure_tiles
     StepGeom geom(int cfg, int mode) const {
-        StepGeom g = geoms[list_index(cfg, mode)];
-        g.grid = step_grid(cfg, g.ntiles, storage, flow, inout, rad, mode & 1);
+        const int li = list_index(cfg, mode);
+        StepGeom g = geoms[li];
+        // one workgroup per tile, dispatched in (XCD-contiguous) tile order, is best for streaming traffic on MI355X
+        g.grid = mode & 1 ? persistent[li] : g.ntiles;
         return g;
     }
 

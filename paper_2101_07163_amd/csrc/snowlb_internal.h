@@ -141,9 +141,8 @@ int tile_config_ty(int i);
 // (FP32 without flow).
 hipError_t launch_step(int tile_cfg, int storage, int flow, int inout, int rad, const DomDesc* doms_dev,
                        const TileDesc* tiles_dev, const StepGeom& geom, bool from_hbm, int par, hipStream_t s, int slot = 0);
-// Grid size of a step launch over `ntiles` tiles: grid_mode 0 = one workgroup per tile,
-// 1 = persistent (one wave of resident workgroups looping over the tiles).
-int step_grid(int tile_cfg, int ntiles, int storage, int flow, int inout, int rad, int grid_mode);
+// Workgroups of a persistent launch over `ntiles` tiles (those resident at a time, looping over the tiles).
+int step_grid(int tile_cfg, int ntiles, int storage, int flow, int inout, int rad);
 // reach of a gradient stencil in cells
 inline int stencil_reach(int stencil) { return stencil >= 6 ? 2 : 1; }
 

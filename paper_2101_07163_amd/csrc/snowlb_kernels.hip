@@ -712,17 +712,14 @@ static int step_lds_pad(int cfg, int flow, int rad) {
     return std::max(0, std::min(65536, 163840 * waves / limit) - used);
 }
 
-// Grid of a step launch.  grid_mode 0: one workgroup per tile, dispatched in (XCD-contiguous) tile
-// order -- measured best for streaming traffic on MI355X.  grid_mode 1: a persistent grid of one
-// wave of resident workgroups that loops over the tiles.
-int step_grid(int cfg, int ntiles, int storage, int flow, int inout, int rad, int grid_mode) {
+// Persistent grid over `ntiles` tiles: one wave of resident workgroups that loops over the tiles, or a workgroup per tile if
+// all are resident.
+int step_grid(int cfg, int ntiles, int storage, int flow, int inout, int rad) {
     void* fn = step_kernel(cfg, storage, flow, inout, rad, true);
     if (!fn || ntiles <= 0) return 0;
-    if (grid_mode == 0) return ntiles;
     int per_cu = 0;
     const int nt = kTiles[cfg].tx * kTiles[cfg].ty;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(fn), nt, 0) !=
-            hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(fn), nt, 0) != hipSuccess ||
         per_cu < 1)
         per_cu = 1;
     int dev = 0, ncu = 256;
@@ -736,16 +733,20 @@ int step_grid(int cfg, int ntiles, int storage, int flow, int inout, int rad, in
 
 hipError_t launch_step(int cfg, int storage, int flow, int inout, int rad, const DomDesc* doms_dev,
                        const TileDesc* tiles_dev, const StepGeom& geom, bool from_hbm, int par, hipStream_t s, int slot) {
-    void* fn = step_kernel(cfg, storage, flow, inout, rad, geom.grid < geom.ntiles);
+    const bool loop = geom.grid < geom.ntiles;
+    void* fn = step_kernel(cfg, storage, flow, inout, rad, loop);
     if (!fn) return hipErrorInvalidValue;
     if (geom.ntiles <= 0) return hipSuccess;
     const int nt = kTiles[cfg].tx * kTiles[cfg].ty;
+    // The wave limit and the pauses are for workgroups that come and go: a persistent grid is the resident set, whose
+    // workgroups neither of them helps (2048^2 FP32 175 us without, 191 with the limit, 184 with the pauses; 1600^2 104,
+    // 113, 106).
+    const bool thin = storage == 0 && from_hbm && !loop;
     StepGeom g = geom;
-    int flags = par | (from_hbm ? 2 : 0) | slot << 2;
+    int flags = par | (thin ? 2 : 0) | slot << 2;
     void* args[] = {(void*)&doms_dev, (void*)&tiles_dev, (void*)&flags, (void*)&g.grid, (void*)&g.ntx, (void*)&g.strip,
                     (void*)&g.per, (void*)&g.m_per, (void*)&g.m_strip, (void*)&g.m_last, (void*)&g.codes, (void*)&g.ntiles};
-    const int pad = storage == 0 && from_hbm ? step_lds_pad(cfg, flow, rad) : 0;
-    return hipLaunchKernel(fn, dim3(g.grid), dim3(nt), args, pad, s);
+    return hipLaunchKernel(fn, dim3(g.grid), dim3(nt), args, thin ? step_lds_pad(cfg, flow, rad) : 0, s);
 }
 
 }  // namespace snowlb
