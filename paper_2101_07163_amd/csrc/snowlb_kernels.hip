@@ -644,10 +644,12 @@ struct TileCfg {
     int tx, ty;
     const char* name;
 };
-static const TileCfg kTiles[] = {
+static constexpr TileCfg kTiles[] = {
     {64, 4, "64x4"}, {64, 8, "64x8"}, {128, 2, "128x2"}, {128, 4, "128x4"}, {64, 2, "64x2"}, {32, 8, "32x8"},
 };
 static constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
+static_assert(kTiles[kTileTwoHigh].tx == 64 && kTiles[kTileTwoHigh].ty == 8 && kTiles[kTileTwoWide].tx == 128 &&
+                  kTiles[kTileTwoWide].ty == 4, "the tiles that the default of 16-bit lattices names");
 
 int tile_config_count() { return kNumTiles; }
 const char* tile_config_name(int i) { return (i >= 0 && i < kNumTiles) ? kTiles[i].name : "?"; }
