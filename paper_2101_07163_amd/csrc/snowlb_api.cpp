@@ -345,11 +345,12 @@ std::string tune_cache_path() {
     return std::string(h ? h : "/tmp") + "/.cache/snowlb_tune.txt";
 }
 
-// Cache lines: "<key> <tile> <grid_mode>" where key is "<layout> nx ny storage flow bc" for one
-// lattice and "<layout> batch <ndomains> <cells> storage flow bc" for a batch; <layout> names the
-// memory layout the timings were taken on, so a library with another layout re-tunes.  The last
-// matching line wins.
-constexpr const char* kTuneLayout = "L7";
+// Cache lines: "<key> <tile> <grid_mode>" where key is "<tag> nx ny storage flow bc reach" for one lattice and "<tag>
+// batch <ndomains> <cells> storage flow bc reach" for a batch.  <tag> names the step kernels, their launch rules and the
+// memory layout the timings were taken on: it changes with any of them, so that another library's picks are not used (the
+// pick for 2048^2 FP16 before tiles of 128 x 4 were the default there, strips of 64 x 4, takes 95 us against 91).
+// The last matching line wins.
+constexpr const char* kTuneTag = "L8";
 // The cache may be shared by several processes: readers take a shared lock, writers an exclusive one.
 bool tune_lookup(const std::string& key, int& tile, int& mode) {
     FILE* f = std::fopen(tune_cache_path().c_str(), "r");
@@ -393,7 +394,7 @@ void tune_store(const std::string& key, int tile, int mode) {
 
 std::string tune_key(const snowlb_params& p) {
     char b[128];
-    std::snprintf(b, sizeof b, "%s %d %d %d %d %d r%d", kTuneLayout, p.nx, p.ny, p.storage, p.flow, p.bc_x,
+    std::snprintf(b, sizeof b, "%s %d %d %d %d %d r%d", kTuneTag, p.nx, p.ny, p.storage, p.flow, p.bc_x,
                   stencil_reach(p.stencil));
     return b;
 }
@@ -1444,7 +1445,7 @@ snowlb_status snowlb_batch_init(snowlb_batch* b, void* stream) {
 static std::string batch_key(const snowlb_batch* b) {
     const snowlb_params& p = b->doms[0]->p;
     char k[160];
-    std::snprintf(k, sizeof k, "%s batch %d %lld %d %d %d r%d", kTuneLayout, (int)b->doms.size(), (long long)b->cells,
+    std::snprintf(k, sizeof k, "%s batch %d %lld %d %d %d r%d", kTuneTag, (int)b->doms.size(), (long long)b->cells,
                   p.storage, p.flow, p.bc_x, stencil_reach(p.stencil));
     return k;
 }
