@@ -32,6 +32,9 @@
  *                          whole graphs cover less than four fifths, calls of fewer than eight graphs on
  *                          more than 2^17 cells, and the rest of others are launched directly
  *   SNOWLB_NO_GRAPH        1: launch every step directly instead of replaying graphs
+ *   SNOWLB_ADJ_KEEP_MIB    MiB that the contexts of the process may together spend on the states that
+ *                          snowlb_adj_forward keeps beyond checkpoints, per device (default 16384; 0:
+ *                          checkpoints only)
  *   SNOWLB_ADJ_OVERLAP     0: run the adjoint backward pass in serial order on the caller's stream
  *                          (default 1: recompute the next checkpoint interval on a second stream of
  *                          the context while the current one is reversed; bitwise the same results)
@@ -229,14 +232,15 @@ int32_t snowlb_get_grid_mode(const snowlb_ctx* ctx);
  *
  * snowlb_adj_forward runs n >= 1 steps from the current state (normally right after snowlb_init),
  * keeping a checkpoint of the state every ckpt_stride steps (0: ceil(sqrt(n)), or every state while
- * the n states take at most 16 GiB and half of the free device memory); afterwards the context holds
- * phi_T (read it with snowlb_read).  snowlb_adj_backward then takes dL/dphi_T
+ * the n states fit in the budget SNOWLB_ADJ_KEEP_MIB and in a quarter of the free device memory);
+ * afterwards the context holds phi_T (read it with snowlb_read).  snowlb_adj_backward then takes dL/dphi_T
  * (ny x nx device field) for any loss L(phi_T) and returns, by the hand-written reverse of each step
  * with the states recomputed from the checkpoints: dL/dU_init (ny x nx device field, the gradient
  * with respect to the initial supersaturation field), dL/deps and dL/dU0 = sum dL/dU_init (host
  * doubles, reduced in FP64 in a fixed order).  Memory: about (n/stride + 2 stride) state copies, or n
  * when every state is kept (nothing is then recomputed, and the results are bitwise the same); it
- * belongs to the context and is reused by later calls.
+ * belongs to the context and is reused by later calls, and kept states are freed by a call that needs less
+ * than half of them.
  * The backward may be called several times after one forward (different dL/dphi_T).  It recomputes
  * checkpoint intervals on a second stream that the context owns (see SNOWLB_ADJ_OVERLAP), ordered
  * after all work queued on `stream` before the call; it returns when the work of both is done. */

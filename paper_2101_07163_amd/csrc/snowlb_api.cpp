@@ -10,6 +10,7 @@
 #include <sys/stat.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -465,6 +466,8 @@ struct snowlb_ctx {
     struct {
         void* slots = nullptr;
         int64_t slot_bytes = 0, nslots = 0;
+        int64_t kept = 0;  // bytes of the slots that count against the budget of kept states, on device `device`
+        int device = 0;
         int n = 0, stride = 0, nck = 0;
         bool have_forward = false;
         bool tape = false;     // the slots hold every state t = 0..n-1 of the forward pass (else checkpoints)
@@ -609,22 +612,49 @@ snowlb_status ctx_alloc(snowlb_ctx* c) {
     return SNOWLB_OK;
 }
 
+// Bytes of kept states (every state of an adjoint forward pass) of all contexts on each device.  They only save
+// recomputation, so the contexts of a process share one budget of SNOWLB_ADJ_KEEP_MIB per device.
+constexpr int kMaxDevices = 64;
+std::atomic<int64_t> g_kept[kMaxDevices];
+int64_t keep_budget() { return (int64_t)std::max(0, env_int("SNOWLB_ADJ_KEEP_MIB", 16384)) << 20; }
+
+// Sets what this context holds of the budget; false (and nothing changed) if that would exceed it.
+bool set_kept(snowlb_ctx* c, int64_t bytes) {
+    if (!c->adj.kept && (hipGetDevice(&c->adj.device) != hipSuccess || c->adj.device < 0 || c->adj.device >= kMaxDevices))
+        return bytes == 0;
+    std::atomic<int64_t>& all = g_kept[c->adj.device];
+    const int64_t more = bytes - c->adj.kept, budget = keep_budget();
+    int64_t held = all.load();
+    do {
+        if (more > 0 && held + more > budget) return false;
+    } while (!all.compare_exchange_weak(held, held + more));
+    c->adj.kept = bytes;
+    return true;
+}
+
 void adj_drop_graphs(snowlb_ctx* c) {
     for (auto& g : c->adj.graphs)
         if (g.exec) (void)hipGraphExecDestroy(g.exec);
     c->adj.graphs.clear();
 }
 
-void adj_free(snowlb_ctx* c) {
-    adj_drop_graphs(c);
+// Frees the slots (which waits for everything queued).
+void adj_free_slots(snowlb_ctx* c) {
+    adj_drop_graphs(c);  // their kernels bake the slots in
     if (c->adj.slots) (void)hipFree(c->adj.slots);
+    c->adj.slots = nullptr;
+    c->adj.nslots = 0;
+}
+
+void adj_free(snowlb_ctx* c) {
+    adj_free_slots(c);
+    (void)set_kept(c, 0);
     if (c->adj.buf) (void)hipFree(c->adj.buf);
     if (c->adj.epart) (void)hipFree(c->adj.epart);
     if (c->adj.rows) (void)hipFree(c->adj.rows);
     if (c->adj.d_out) (void)hipFree(c->adj.d_out);
     if (c->adj.h_out) (void)hipHostFree(c->adj.h_out);
     if (c->adj.d_segdoms) (void)hipFree(c->adj.d_segdoms);
-    c->adj.slots = nullptr;
     c->adj.buf = nullptr;
     c->adj.epart = c->adj.rows = c->adj.d_out = c->adj.h_out = nullptr;
     c->adj.d_segdoms = nullptr;
@@ -635,7 +665,6 @@ void adj_free(snowlb_ctx* c) {
         }
     if (c->adj.rstream) (void)hipStreamDestroy(c->adj.rstream);
     c->adj.rstream = nullptr;
-    c->adj.nslots = 0;
     c->adj.segdoms_valid = false;
     c->adj.have_forward = false;
 }
@@ -1011,28 +1040,40 @@ static int64_t adj_cells(const snowlb_ctx* c) { return (int64_t)c->dom.nbx * kBl
 // First slot of segment area a (two areas of `stride` states follow the checkpoints).
 static int64_t adj_area_slot(const snowlb_ctx* c, int a) { return (int64_t)c->adj.nck + (int64_t)a * c->adj.stride; }
 
-// Slots for `need` states: kept from an earlier call if there are enough.
-static snowlb_status adj_slots(snowlb_ctx* c, int64_t need, int64_t slot_bytes) {
-    if (c->adj.nslots >= need && c->adj.slot_bytes == slot_bytes) return SNOWLB_OK;
-    adj_drop_graphs(c);  // their kernels bake the slots in
-    if (c->adj.slots) (void)hipFree(c->adj.slots);
-    c->adj.slots = nullptr;
-    c->adj.nslots = 0;
-    HIPCHK(c, hipMalloc(&c->adj.slots, (size_t)(need * slot_bytes)));
+// Whether the slots of an earlier call serve for `need` states: there are enough, and not kept states of which less than
+// half are needed (those are given back).
+static bool adj_slots_serve(const snowlb_ctx* c, int64_t need, int64_t slot_bytes) {
+    return c->adj.nslots >= need && c->adj.slot_bytes == slot_bytes && (!c->adj.kept || 2 * need >= c->adj.nslots);
+}
+
+static snowlb_status adj_alloc_slots(snowlb_ctx* c, int64_t need, int64_t slot_bytes) {
+    adj_free_slots(c);
+    const hipError_t e = hipMalloc(&c->adj.slots, (size_t)(need * slot_bytes));
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        c->adj.slots = nullptr;
+        (void)set_kept(c, 0);
+        return hip_fail(c, e, "hipMalloc(adjoint states)");
+    }
     c->adj.nslots = need;
     c->adj.slot_bytes = slot_bytes;
     return SNOWLB_OK;
 }
 
-// Whether the forward pass keeps every state: the caller left the checkpoint stride to the library, and the states
-// fit in kTapeBytes and in half of the memory that is free (or are there from an earlier call).
-constexpr int64_t kTapeBytes = int64_t(16) << 30;
-static bool adj_tape_fits(const snowlb_ctx* c, int n, int stride, int64_t slot_bytes) {
-    if (stride > 0 || (int64_t)n * slot_bytes > kTapeBytes) return false;
-    if (c->adj.nslots >= n && c->adj.slot_bytes == slot_bytes) return true;
+// Slots for every state of n steps, if the caller left the checkpoint stride to the library and they fit in the budget and in a
+// quarter of the free memory (what checkpointing would take, `checkpoints` states, is not counted).
+static bool adj_keep_states(snowlb_ctx* c, int n, int stride, int64_t checkpoints, int64_t slot_bytes) {
+    const int64_t bytes = (int64_t)n * slot_bytes, before = c->adj.kept;
+    if (stride > 0 || bytes > keep_budget()) return false;
+    if (adj_slots_serve(c, n, slot_bytes)) return true;
+    if (!set_kept(c, n > checkpoints ? bytes : 0)) return false;
     size_t free_bytes = 0, total = 0;
-    if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) return false;
-    return (int64_t)n * slot_bytes <= (int64_t)(free_bytes / 2);
+    if (n > checkpoints && (hipMemGetInfo(&free_bytes, &total) != hipSuccess ||
+                            bytes > (int64_t)(free_bytes / 4) + c->adj.nslots * c->adj.slot_bytes)) {
+        (void)set_kept(c, before);
+        return false;
+    }
+    return adj_alloc_slots(c, n, slot_bytes) == SNOWLB_OK;
 }
 
 // The step descriptors from the context's current domain (eps may have changed) and slot layout: step i of a
@@ -1092,11 +1133,11 @@ snowlb_status snowlb_adj_forward(snowlb_ctx* c, int32_t n, int32_t stride, void*
     c->adj.n = n;
     c->adj.stride = st;
     c->adj.nck = nck;
-    c->adj.tape = adj_tape_fits(c, n, stride, slot_bytes) && adj_slots(c, n, slot_bytes) == SNOWLB_OK;
-    if (!c->adj.tape) {
-        (void)hipGetLastError();  // of a tape that could not be allocated
-        // checkpoints, then two segment areas
-        if (snowlb_status r = adj_slots(c, (int64_t)nck + 2 * (int64_t)st, slot_bytes)) return r;
+    const int64_t checkpoints = (int64_t)nck + 2 * (int64_t)st;  // checkpoints, then two segment areas
+    c->adj.tape = adj_keep_states(c, n, stride, checkpoints, slot_bytes);
+    if (!c->adj.tape && !adj_slots_serve(c, checkpoints, slot_bytes)) {
+        (void)set_kept(c, 0);
+        if (snowlb_status r = adj_alloc_slots(c, checkpoints, slot_bytes)) return r;
     }
     if (snowlb_status r = from_driver(c, c->drv.ensure_tiles(c->drv.tile, c->drv.grid_mode))) return r;
     if (snowlb_status r = adj_descriptors(c)) return r;

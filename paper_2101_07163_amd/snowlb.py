@@ -534,7 +534,9 @@ def _adjoint_function():
         """phi_T = SnowAdjoint.apply(eps, U_init, sim, n_steps, ckpt_stride).
 
         Forward: set eps, initialise the context `sim` (no flow, periodic, FP32) with the initial
-        supersaturation field U_init, run n_steps with checkpoints every ckpt_stride steps (0: sqrt).
+        supersaturation field U_init, run n_steps with checkpoints every ckpt_stride steps (0: every state is
+        kept while the states fit in the budget SNOWLB_ADJ_KEEP_MIB, 16 GiB by default for all contexts together, and in
+        a quarter of the free memory; else sqrt(n_steps)).
         Backward: the library's hand-written adjoint gives dL/deps and dL/dU_init from dL/dphi_T;
         gradients with respect to anything U_init was built from (e.g. U0) follow by autograd.
         """
