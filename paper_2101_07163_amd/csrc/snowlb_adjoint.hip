@@ -19,6 +19,8 @@
 // side per 64 x 4 block); lambda of g_0..4, h_0..8 uses the same order, lambda of phi_prev is a plane
 // of its own.
 #include <hip/hip_runtime.h>
+
+#include <cstring>
 #include <stdint.h>
 
 #include "snowlb_internal.h"
@@ -384,6 +386,23 @@ static int adj_rows(const AdjDesc& A) {
     return 8 * t >= 7 * slots ? 16 : 8;
 }
 int adj_blocks(const AdjDesc& A) { return adj_tiles(A, adj_rows(A)); }
+
+struct DescriptorPair {
+    DomDesc d[2];
+};
+constexpr int kPairWords = sizeof(DescriptorPair) / 4;
+static_assert(kPairWords <= 256 && sizeof(DescriptorPair) % 4 == 0, "a word per lane");
+__global__ void __launch_bounds__(256) k_put_descriptors(uint32_t* __restrict__ dst, DescriptorPair pair) {
+    if (threadIdx.x < kPairWords) dst[threadIdx.x] = reinterpret_cast<const uint32_t*>(&pair)[threadIdx.x];
+}
+
+hipError_t launch_put_descriptors(DomDesc* dst, const DomDesc& a, const DomDesc& b, hipStream_t s) {
+    DescriptorPair pair;
+    std::memcpy((void*)&pair.d[0], (const void*)&a, sizeof a);
+    std::memcpy((void*)&pair.d[1], (const void*)&b, sizeof b);
+    hipLaunchKernelGGL(k_put_descriptors, dim3(1), dim3(256), 0, s, reinterpret_cast<uint32_t*>(dst), pair);
+    return hipGetLastError();
+}
 
 hipError_t launch_adj_seed(const AdjDesc& A, const float* dphi, hipStream_t s) {
     hipLaunchKernelGGL(k_adj_seed, dim3((A.nx + 255) / 256, A.ny), dim3(256), 0, s, A, dphi);

@@ -478,10 +478,8 @@ struct snowlb_ctx {
         double* d_out = nullptr;
         double* h_out = nullptr;  // pinned, 2 doubles
         // step descriptors: of the two segment areas, of the tape, and of the forward pass's last step, which
-        // writes the context's copy 0; and what of them is on the device
+        // writes the context's copy 0
         DomDesc* d_segdoms = nullptr;
-        DomDesc segdoms[4];
-        bool segdoms_valid = false;
         // the backward pass recomputes the next interval on its own stream while the current one is
         // reversed; events order the two (index: segment area)
         hipStream_t rstream = nullptr;
@@ -665,7 +663,6 @@ void adj_free(snowlb_ctx* c) {
         }
     if (c->adj.rstream) (void)hipStreamDestroy(c->adj.rstream);
     c->adj.rstream = nullptr;
-    c->adj.segdoms_valid = false;
     c->adj.have_forward = false;
 }
 
@@ -1077,35 +1074,29 @@ static bool adj_keep_states(snowlb_ctx* c, int n, int stride, int64_t checkpoint
 }
 
 // The step descriptors from the context's current domain (eps may have changed) and slot layout: step i of a
-// segment area or of the tape reads slot i of it and writes slot i + 1.  They are uploaded only when they
-// differ from those on the device, once nothing queued can read them any more.
-static snowlb_status adj_descriptors(snowlb_ctx* c) {
-    DomDesc h[4];
-    std::memset((void*)h, 0, sizeof h);  // padding too: they are compared as bytes
-    auto set = [&](int k, char* from, char* to) {
-        std::memcpy((void*)&h[k], (const void*)&c->dom, sizeof(DomDesc));
-        h[k].pop[0] = from;
-        h[k].pop[1] = to;
-        h[k].phip[0] = (float*)(from + c->pop_bytes);
-        h[k].phip[1] = (float*)(to + c->pop_bytes);
-        h[k].slot_stride = c->adj.slot_bytes;
+// segment area or of the tape reads slot i of it and writes slot i + 1.  Written in the order of the stream by every pass
+// that uses them, so no pass waits for the device and none depends on what an earlier one left.
+static snowlb_status adj_descriptors(snowlb_ctx* c, hipStream_t s) {
+    DomDesc h[2] = {c->dom, c->dom};
+    auto set = [&](DomDesc& d, char* from, char* to) {
+        d.pop[0] = from;
+        d.pop[1] = to;
+        d.phip[0] = (float*)(from + c->pop_bytes);
+        d.phip[1] = (float*)(to + c->pop_bytes);
+        d.slot_stride = c->adj.slot_bytes;
     };
     if (c->adj.tape) {
-        set(2, adj_slot(c, 0), adj_slot(c, 1));
-        set(3, adj_slot(c, c->adj.n - 1), adj_slot(c, 0));
-        h[3].pop[1] = c->dom.pop[0];
-        h[3].phip[1] = c->dom.phip[0];
-        h[3].slot_stride = 0;
+        set(h[0], adj_slot(c, 0), adj_slot(c, 1));
+        set(h[1], adj_slot(c, c->adj.n - 1), adj_slot(c, 0));
+        h[1].pop[1] = c->dom.pop[0];
+        h[1].phip[1] = c->dom.phip[0];
+        h[1].slot_stride = 0;
     } else {
-        for (int ar = 0; ar < 2; ++ar) set(ar, adj_slot(c, adj_area_slot(c, ar)), adj_slot(c, adj_area_slot(c, ar) + 1));
+        for (int ar = 0; ar < 2; ++ar) set(h[ar], adj_slot(c, adj_area_slot(c, ar)), adj_slot(c, adj_area_slot(c, ar) + 1));
     }
-    if (c->adj.segdoms_valid && std::memcmp((const void*)h, (const void*)c->adj.segdoms, sizeof h) == 0) return SNOWLB_OK;
-    c->adj.segdoms_valid = false;
-    HIPCHK(c, hipDeviceSynchronize());
-    if (!c->adj.d_segdoms) HIPCHK(c, hipMalloc(&c->adj.d_segdoms, sizeof h));
-    HIPCHK(c, hipMemcpy(c->adj.d_segdoms, h, sizeof h, hipMemcpyHostToDevice));
-    std::memcpy((void*)c->adj.segdoms, (const void*)h, sizeof h);
-    c->adj.segdoms_valid = true;
+    if (!c->adj.d_segdoms) HIPCHK(c, hipMalloc(&c->adj.d_segdoms, 4 * sizeof(DomDesc)));
+    const hipError_t e = launch_put_descriptors(c->adj.d_segdoms + (c->adj.tape ? 2 : 0), h[0], h[1], s);
+    if (e != hipSuccess) return hip_fail(c, e, "descriptor kernel");
     return SNOWLB_OK;
 }
 
@@ -1140,7 +1131,6 @@ snowlb_status snowlb_adj_forward(snowlb_ctx* c, int32_t n, int32_t stride, void*
         if (snowlb_status r = adj_alloc_slots(c, checkpoints, slot_bytes)) return r;
     }
     if (snowlb_status r = from_driver(c, c->drv.ensure_tiles(c->drv.tile, c->drv.grid_mode))) return r;
-    if (snowlb_status r = adj_descriptors(c)) return r;
     auto keep = [&](int64_t slot) -> snowlb_status {
         char* sl = adj_slot(c, slot);
         HIPCHK(c, hipMemcpyAsync(sl, c->dom.pop[c->drv.par], c->pop_bytes, hipMemcpyDeviceToDevice, s));
@@ -1151,6 +1141,7 @@ snowlb_status snowlb_adj_forward(snowlb_ctx* c, int32_t n, int32_t stride, void*
         // Every state is kept where its step writes it, so the backward pass recomputes nothing and neither pass
         // copies checkpoints (512^2, 100 steps, both passes: 3.0 -> 2.0 ms).
         c->adj.tape_eps = c->dom.eps;
+        if (snowlb_status r = adj_descriptors(c, s)) return r;
         if (snowlb_status r = keep(0)) return r;
         if (snowlb_status r = adj_tape_steps(c, 0, n - 1, s)) return r;
         Driver& D = c->drv;
@@ -1283,7 +1274,9 @@ snowlb_status snowlb_adj_backward(snowlb_ctx* c, const float* dphi, float* dU, d
         HIPCHK(c, hipHostMalloc(&c->adj.h_out, 2 * sizeof(double), hipHostMallocDefault));
     }
     const int st = c->adj.stride, n = c->adj.n;
-    if (snowlb_status r2 = adj_descriptors(c)) return r2;
+    // (kept states are only recomputed after a change of eps)
+    if (!c->adj.tape || c->adj.tape_eps != c->dom.eps)
+        if (snowlb_status r2 = adj_descriptors(c, s)) return r2;
     float* lam[2] = {c->adj.buf, c->adj.buf + (kAdjPlanes + 1) * cells};
     A.epart = c->adj.epart;
     HIPCHK(c, hipMemsetAsync(c->adj.epart, 0, (size_t)nblk * sizeof(double), s));

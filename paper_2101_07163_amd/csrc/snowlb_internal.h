@@ -177,6 +177,8 @@ struct AdjDesc {
 };
 constexpr int kAdjPlanes = 14;  // g_0..4, h_0..8 of the no-flow state
 int adj_blocks(const AdjDesc& A);
+// dst[0] = a, dst[1] = b, in the order of the stream (the values travel with the launch)
+hipError_t launch_put_descriptors(DomDesc* dst, const DomDesc& a, const DomDesc& b, hipStream_t s);
 hipError_t launch_adj_seed(const AdjDesc& A, const float* dphi, hipStream_t s);
 hipError_t launch_adj_step(const AdjDesc& A, hipStream_t s);
 // dU[y*nx + x] = dL/dU_init; rows: ny doubles of scratch; out[0] = dL/deps, out[1] = sum dU
