@@ -66,7 +66,7 @@ struct Driver {
     const DomDesc* d_doms = nullptr;  // owned by the caller
     std::vector<const DomDesc*> h_doms;  // host copies (geometry for the tile lists)
     int storage = 0, flow = 0, inout = 0, rad = 1;
-    bool from_hbm = false;  // the two copies of all lattices exceed the last-level cache
+    int hbm = 0;  // the two copies of all lattices exceed the last-level cache (1), and twice that (2)
     int64_t cells = 0;      // of all lattices
     // grid_mode (launch mode): bit 0 = persistent grid (else one workgroup per tile), grid_mode >> 1 =
     // tile order; see ensure_tiles
@@ -111,7 +111,7 @@ struct Driver {
             cells += (int64_t)d->nx * d->ny;
             bytes += 2 * (int64_t)d->nbx * kBlockX * round_up(d->ny, kBlockY) * (d->nqb * (d->storage == SNOWLB_STORE_FP32 ? 4 : 2) + 4);
         }
-        from_hbm = bytes > kLastLevelCache;
+        hbm = (bytes > kLastLevelCache) + (bytes > 2 * kLastLevelCache);
         d_tiles.assign(kTileOrders * tile_config_count(), nullptr);
         geoms.assign(kTileOrders * tile_config_count(), StepGeom{});
         persistent.assign(kTileOrders * tile_config_count(), 0);
@@ -130,7 +130,7 @@ struct Driver {
     // us, 22.5 with 128 x 4 and 21.6 with 64 x 8; 1523 x 1101 31.2, 32.5, 31.8), and in FP32, where a tile row is two
     // lines (2048^2 148.0, 151.4, 152.9).
     int default_tile() const {
-        if (storage == SNOWLB_STORE_FP32 || !from_hbm) return 0;
+        if (storage == SNOWLB_STORE_FP32 || !hbm) return 0;
         int64_t one = 0, two = 0;  // lanes of tiles one and two blocks wide
         for (const DomDesc* d : h_doms) {
             const int64_t rows = round_up(d->ny, kBlockY);
@@ -219,7 +219,7 @@ struct Driver {
         const int li = list_index(cfg, mode);
         const StepGeom g = geom(cfg, mode);
         for (int i = 0; i < n; ++i) {
-            hipError_t e = launch_step(cfg, storage, flow, inout, rad, d_doms, d_tiles[li], g, from_hbm, par, s);
+            hipError_t e = launch_step(cfg, storage, flow, inout, rad, d_doms, d_tiles[li], g, hbm, par, s);
             if (e != hipSuccess) return hipfail(e, "step kernel launch");
             par ^= 1;
             step += 1;
@@ -240,7 +240,7 @@ struct Driver {
         if (e != hipSuccess) return hipfail(e, "hipStreamBeginCapture");
         hipError_t le = hipSuccess;
         for (int i = 0; i < K && le == hipSuccess; ++i)
-            le = launch_step(tile, storage, flow, inout, rad, d_doms, d_tiles[li], sg, from_hbm, i & 1,
+            le = launch_step(tile, storage, flow, inout, rad, d_doms, d_tiles[li], sg, hbm, i & 1,
                              cap_stream);
         hipGraph_t g = nullptr;
         hipError_t ee = hipStreamEndCapture(cap_stream, &g);
@@ -1105,7 +1105,7 @@ static snowlb_status adj_tape_steps(snowlb_ctx* c, int first, int last, hipStrea
     Driver& D = c->drv;
     const StepGeom sg = D.geom(D.tile, D.grid_mode);
     for (int i = first; i < last; ++i) {
-        const hipError_t e = launch_step(D.tile, c->p.storage, 0, 0, 1, c->adj.d_segdoms + 2, nullptr, sg, D.from_hbm, 0, s, i);
+        const hipError_t e = launch_step(D.tile, c->p.storage, 0, 0, 1, c->adj.d_segdoms + 2, nullptr, sg, D.hbm, 0, s, i);
         if (e != hipSuccess) return hip_fail(c, e, "adjoint tape step");
     }
     return SNOWLB_OK;
@@ -1146,7 +1146,7 @@ snowlb_status snowlb_adj_forward(snowlb_ctx* c, int32_t n, int32_t stride, void*
         if (snowlb_status r = adj_tape_steps(c, 0, n - 1, s)) return r;
         Driver& D = c->drv;
         const hipError_t e = launch_step(D.tile, c->p.storage, 0, 0, 1, c->adj.d_segdoms + 3, nullptr,
-                                         D.geom(D.tile, D.grid_mode), D.from_hbm, 0, s);
+                                         D.geom(D.tile, D.grid_mode), D.hbm, 0, s);
         if (e != hipSuccess) return hip_fail(c, e, "adjoint tape step");
         D.par = 0;
         D.step += n;
@@ -1210,7 +1210,7 @@ static snowlb_status adj_graph(snowlb_ctx* c, int kind, AdjDesc A, float* const 
     if (kind == 0) {
         const StepGeom sg = D.geom(D.tile, D.grid_mode);
         for (int i = 0; i + 1 < len && le == hipSuccess; ++i)
-            le = launch_step(D.tile, c->p.storage, 0, 0, 1, c->adj.d_segdoms + area, nullptr, sg, D.from_hbm, 0, cs, i);
+            le = launch_step(D.tile, c->p.storage, 0, 0, 1, c->adj.d_segdoms + area, nullptr, sg, D.hbm, 0, cs, i);
     } else {
         const int64_t base = adj_area_slot(c, area);
         for (int i = len - 1; i >= 0 && le == hipSuccess; --i) {

@@ -136,11 +136,11 @@ int tile_config_tx(int i);
 int tile_config_ty(int i);
 // One step of every tile of `geom` (of the list `tiles_dev`, or with tiles_dev null those of the single lattice
 // doms_dev[0]), reading copy `par` and writing copy 1 - par.  `flow`, `inout`, `storage` and the gradient reach
-// `rad` (1 for E2/E4, 2 for E6/E8) must be the same for every domain referenced.  `from_hbm`: the two copies of
-// the lattices exceed the last-level cache.  `slot`: step of a tape, whose copies lie slot * slot_stride bytes on
+// `rad` (1 for E2/E4, 2 for E6/E8) must be the same for every domain referenced.  `hbm`: the two copies of the
+// lattices exceed the last-level cache (1), and twice that (2).  `slot`: step of a tape, whose copies lie slot * slot_stride bytes on
 // (FP32 without flow).
 hipError_t launch_step(int tile_cfg, int storage, int flow, int inout, int rad, const DomDesc* doms_dev,
-                       const TileDesc* tiles_dev, const StepGeom& geom, bool from_hbm, int par, hipStream_t s, int slot = 0);
+                       const TileDesc* tiles_dev, const StepGeom& geom, int hbm, int par, hipStream_t s, int slot = 0);
 // Workgroups of a persistent launch over `ntiles` tiles (those resident at a time, looping over the tiles).
 int step_grid(int tile_cfg, int ntiles, int storage, int flow, int inout, int rad);
 // reach of a gradient stencil in cells

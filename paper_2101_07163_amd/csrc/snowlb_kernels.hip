@@ -560,10 +560,13 @@ k_step(const DomDesc* __restrict__ doms, const TileDesc* __restrict__ tiles, int
             }
 
             // ---- push streaming into copy 1 - par.  Population q goes to the lane offset xd of row y + c_y, where
-            // h'_q takes h_q of the LDS position li.  On lattices beyond the last-level cache (bit 1 of flags)
-            // FP32 waves pause 6 x 64 cycles before each direction's stores: all stores in one burst hold up the
+            // h'_q takes h_q of the LDS position li.  On lattices of more than twice the last-level cache (bit 1 of
+            // flags) FP32 waves pause 6 x 64 cycles before each direction's stores: all stores in one burst hold up the
             // loads of the CU's other workgroups (64-crystal batch 947 -> 900 us, 3000^2 331 -> 323, 2048^2 151
             // -> 148.5; pauses of 3 or 4 are worth less, 9 no more; without flow and in 16 bits they only cost).
+            // Between one and two caches they cost too: 1600^2 (501 MB) 92.6 us, 89.5 without, 65 x 20001 (492 MB)
+            // 75.5 and 73.3, 1200^2 (288 MB) 47.6 and 47.3; from there on they are worth nothing or more (1750^2, 602 MB,
+            // 111.7 and 111.8).
             const bool paced = FLOW && !REF && (flags & 2);
             auto push = [&](int q, uint32_t xd, int li) {
                 if (paced) __builtin_amdgcn_s_sleep(6);
@@ -734,7 +737,7 @@ int step_grid(int cfg, int ntiles, int storage, int flow, int inout, int rad) {
 }
 
 hipError_t launch_step(int cfg, int storage, int flow, int inout, int rad, const DomDesc* doms_dev,
-                       const TileDesc* tiles_dev, const StepGeom& geom, bool from_hbm, int par, hipStream_t s, int slot) {
+                       const TileDesc* tiles_dev, const StepGeom& geom, int hbm, int par, hipStream_t s, int slot) {
     const bool loop = geom.grid < geom.ntiles;
     void* fn = step_kernel(cfg, storage, flow, inout, rad, loop);
     if (!fn) return hipErrorInvalidValue;
@@ -743,9 +746,9 @@ hipError_t launch_step(int cfg, int storage, int flow, int inout, int rad, const
     // The wave limit and the pauses are for workgroups that come and go: a persistent grid is the resident set, whose
     // workgroups neither of them helps (2048^2 FP32 175 us without, 191 with the limit, 184 with the pauses; 1600^2 104,
     // 113, 106).
-    const bool thin = storage == 0 && from_hbm && !loop;
+    const bool thin = storage == 0 && hbm && !loop;
     StepGeom g = geom;
-    int flags = par | (thin ? 2 : 0) | slot << 2;
+    int flags = par | (thin && hbm > 1 ? 2 : 0) | slot << 2;
     void* args[] = {(void*)&doms_dev, (void*)&tiles_dev, (void*)&flags, (void*)&g.grid, (void*)&g.ntx, (void*)&g.strip,
                     (void*)&g.per, (void*)&g.m_per, (void*)&g.m_strip, (void*)&g.m_last, (void*)&g.codes, (void*)&g.ntiles};
     return hipLaunchKernel(fn, dim3(g.grid), dim3(nt), args, thin ? step_lds_pad(cfg, flow, rad) : 0, s);
