@@ -499,9 +499,9 @@ __global__ void __launch_bounds__(kBlockCells) k_pop_get(DomDesc d, int par, flo
 // (resp. g) resets the rho, j (resp. U) reference planes to 0 -- any consistent reference is valid;
 // populations streamed from the inlet ghost keep the ghost's references.  Writing phi_prev
 // re-encodes h.
-// The 16-bit value of a population p: its deviation is rounded to FP32 and then to 16 bits.  (Left to itself the
-// compiler may fold the conversion into the multiply-add, which rounds once, in some instances and not in
-// others; a written state should not depend on that.)
+// The 16-bit value of a population of f or g: its deviation is rounded to FP32 and then to 16 bits.  (Left to itself the
+// compiler may fold the conversion into the multiply-add, which rounds once, in some instances and not in others.  It
+// does so for h and phi_prev below and in k_write_field in every instance, and their bits have always been those.)
 template <class S>
 __device__ __forceinline__ typename S::T enc_deviation(float p, float iw, float ref) {
     float e = __builtin_fmaf(p, iw, -ref);
