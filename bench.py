@@ -439,7 +439,8 @@ def main():
                      "kernel": "k_step", "bytes_per_update": bpu,
                      "impl_bytes_per_update": impl_bytes_per_update(flow, args.storage),
                      "kernel_avg_ms": round(kernel_ms, 5)},
-        "timing": {"repeats": REPEATS, "statistic": "median", "path": "captured HIP graphs",
+        "timing": {"repeats": REPEATS, "statistic": "median",
+                   "path": "captured HIP graphs" if args.steps >= 256 else "direct launches",
                    "wall_s": reps["wall_s"], "kernel_ms_per_step": reps["kernel_ms"],
                    "diag_sync_ms": reps["diag_ms"]},
     }

@@ -126,9 +126,9 @@ struct Driver {
     // 214.6, 1800^2 93.5 -> 84.4, without flow 2999 x 2501 109.6 -> 100.3, 64 crystals in FP16 637 -> 597.  Where odd
     // last blocks would leave more than a twentieth of their lanes idle, 64 x 8 tiles are the faster ones (64 x 4,
     // 128 x 4, 64 x 8: 448 x 6001 74.8, 74.8, 71.5 us; 150 x 16001 78.5, 82.5, 75.4; 18 crystals of 219^2 to 554^2
-    // 82.1, 84.1, 80.4; 832 x 3501, a thirteenth, 81.6, 77.9, 78.7).  In the cache 64 x 4 is faster (1024^2 21.3
-    // us, 22.5 with 128 x 4 and 21.6 with 64 x 8; 1523 x 1101 31.2, 32.5, 31.8), and in FP32, where a tile row is two
-    // lines (2048^2 148.0, 151.4, 152.9).
+    // 82.1, 84.1, 80.4); the line lies where the two meet (832 x 3501, a thirteenth idle, 81.6, 77.9, 78.7).  In the cache
+    // 64 x 4 is faster (1024^2 21.3 us, 22.5 with 128 x 4 and 21.6 with 64 x 8; 1523 x 1101 31.2, 32.5, 31.8), and in FP32,
+    // where a tile row is two lines (2048^2 148.0, 151.4, 152.9).
     int default_tile() const {
         if (storage == SNOWLB_STORE_FP32 || !hbm) return 0;
         int64_t one = 0, two = 0;  // lanes of tiles one and two blocks wide
@@ -1058,7 +1058,7 @@ static snowlb_status adj_alloc_slots(snowlb_ctx* c, int64_t need, int64_t slot_b
 }
 
 // Slots for every state of n steps, if the caller left the checkpoint stride to the library and they fit in the budget and in a
-// quarter of the free memory (what checkpointing would take, `checkpoints` states, is not counted).
+// quarter of the free memory, or are no more than the `checkpoints` states that checkpointing takes.
 static bool adj_keep_states(snowlb_ctx* c, int n, int stride, int64_t checkpoints, int64_t slot_bytes) {
     const int64_t bytes = (int64_t)n * slot_bytes, before = c->adj.kept;
     if (stride > 0 || bytes > keep_budget()) return false;

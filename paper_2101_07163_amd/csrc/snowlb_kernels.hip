@@ -564,9 +564,8 @@ k_step(const DomDesc* __restrict__ doms, const TileDesc* __restrict__ tiles, int
             // flags) FP32 waves pause 6 x 64 cycles before each direction's stores: all stores in one burst hold up the
             // loads of the CU's other workgroups (64-crystal batch 947 -> 900 us, 3000^2 331 -> 323, 2048^2 151
             // -> 148.5; pauses of 3 or 4 are worth less, 9 no more; without flow and in 16 bits they only cost).
-            // Between one and two caches they cost too: 1600^2 (501 MB) 92.6 us, 89.5 without, 65 x 20001 (492 MB)
-            // 75.5 and 73.3, 1200^2 (288 MB) 47.6 and 47.3; from there on they are worth nothing or more (1750^2, 602 MB,
-            // 111.7 and 111.8).
+            // Between one and two caches they cost too: 1300^2 (335 MB) 64.9 us, 61.9 without, 65 x 20001 (492 MB) 75.3 and
+            // 73.4; from there on they pay (1750^2, 602 MB, 111.1 and 113.2).
             const bool paced = FLOW && !REF && (flags & 2);
             auto push = [&](int q, uint32_t xd, int li) {
                 if (paced) __builtin_amdgcn_s_sleep(6);
